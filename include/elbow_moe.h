@@ -242,20 +242,18 @@ int elb_moe_forward_noalloc(const void *x, const void *W_router, const void *W_g
                             float *w_out, int32_t *counts_out, void *stream);
 
 /*
- * Packed expert weights for decode-sized batches.  When an expert gets at most 16 rows on
- * average (T K <= 16 N), the expert GEMMs are bound by reading the weights; the layer then
- * streams each expert's weights in 64-row tasks.  elb_pack_expert_weights writes a copy of
- * W_gate_up and W_down in exactly that streaming order (per task, stage and MFMA operand, the
- * 64 lanes' 16-byte pieces contiguous), so that every load reads 1 KB contiguous; it is done
- * once, outside the per-call path.  The packed copy has the size of the two weight tensors
- * together (elb_packed_expert_bytes), is bf16 only (d % 64 == 0, m % 64 == 0) and is valid
- * until the weights change.
+ * Packed expert weights.  elb_pack_expert_weights writes a copy of W_gate_up and W_down in
+ * MFMA operand order (per 64-row task, 64-deep stage, 32-deep half and 16-row fragment the 64
+ * lanes' 16-byte pieces contiguous): the order an operand-streaming kernel loads in.  The
+ * packed copy has the size of the two weight tensors together (elb_packed_expert_bytes) and
+ * is bf16 only (d % 64 == 0, m % 64 == 0).
  *   W_gate_up [N, 2m, d], W_down [N, d, m]   bf16 input (as for elb_moe_experts)
  *   packed                                   device output, elb_packed_expert_bytes bytes
  * elb_moe_experts_packed / elb_moe_forward_packed are elb_moe_experts / elb_moe_forward with
- * that copy as an extra argument: the decode-sized kernels read it, every other path reads
- * W_gate_up and W_down as usual (so both are still required).  Results are bit-identical to
- * the unpacked calls.
+ * that copy (or NULL) as an extra argument.  The decode-sized kernels now stream the row-major
+ * weights at the rate they once needed the copy for, so every path reads W_gate_up and W_down
+ * (both are required, as before) and the copy is not read: results are bit-identical to the
+ * unpacked calls, and a program can save the copy's memory.
  */
 size_t elb_packed_expert_bytes(int32_t N, int32_t d, int32_t m);
 int elb_pack_expert_weights(const void *W_gate_up, const void *W_down, int32_t N, int32_t d,

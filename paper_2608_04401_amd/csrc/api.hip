@@ -366,7 +366,6 @@ size_t elb_moe_workspace_bytes(int64_t T, int32_t d, int32_t N, int32_t m, int32
 }
 
 static int experts_impl(const void* x, const void* W_gate_up, const void* W_down,
-                        const void* packed,
                         const int32_t* k, const int32_t* ids, const float* w,
                         const void* residual, int64_t T, int d, int N, int m, int K, int dtype,
                         void* y, char* ws, const Layout& L, int32_t* counts_out,
@@ -390,8 +389,8 @@ static int experts_impl(const void* x, const void* W_gate_up, const void* W_down
     if (gemm_use_skinny(dtype, T, K, N, d, m)) {
         // decode-sized: no dispatch; the expert waves find their slots from (k, ids) and
         // write rows t K + j of H and Y, which the combine reads directly
-        if (int rc = hip_status(launch_gemm_skinny(x, W_gate_up, W_down, packed, k, ids, T, K,
-                                                   d, N, m, H, Y, counts_out, s),
+        if (int rc = hip_status(launch_gemm_skinny(x, W_gate_up, W_down, k, ids, T, K, d, N,
+                                                   m, H, Y, counts_out, s),
                                 "gemm_skinny"))
             return rc;
         return hip_status(launch_combine(Y, k, nullptr, w, residual, T, d, K, dtype, y, s),
@@ -419,7 +418,7 @@ static int experts_impl(const void* x, const void* W_gate_up, const void* W_down
 }
 
 static int moe_experts_entry(const void* x, const void* W_gate_up, const void* W_down,
-                             const void* packed, const int32_t* k, const int32_t* ids,
+                             const int32_t* k, const int32_t* ids,
                              const float* w, const void* residual, int64_t T, int32_t d,
                              int32_t N, int32_t m, int32_t K, int32_t dtype, void* y,
                              void* workspace, size_t workspace_bytes, void* stream) {
@@ -434,7 +433,7 @@ static int moe_experts_entry(const void* x, const void* W_gate_up, const void* W
                     L.experts_end);
     if ((uintptr_t)workspace % kAlign)
         return fail(ELB_ERR_WORKSPACE, "workspace not %zu-byte aligned", kAlign);
-    return experts_impl(x, W_gate_up, W_down, packed, k, ids, w, residual, T, d, N, m, K,
+    return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                         dtype, y, (char*)workspace, L, nullptr, (hipStream_t)stream);
 }
 
@@ -442,7 +441,7 @@ int elb_moe_experts(const void* x, const void* W_gate_up, const void* W_down,
                     const int32_t* k, const int32_t* ids, const float* w, const void* residual,
                     int64_t T, int32_t d, int32_t N, int32_t m, int32_t K, int32_t dtype,
                     void* y, void* workspace, size_t workspace_bytes, void* stream) {
-    return moe_experts_entry(x, W_gate_up, W_down, nullptr, k, ids, w, residual, T, d, N, m, K,
+    return moe_experts_entry(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                              dtype, y, workspace, workspace_bytes, stream);
 }
 
@@ -451,12 +450,13 @@ int elb_moe_experts_packed(const void* x, const void* W_gate_up, const void* W_d
                            const float* w, const void* residual, int64_t T, int32_t d,
                            int32_t N, int32_t m, int32_t K, int32_t dtype, void* y,
                            void* workspace, size_t workspace_bytes, void* stream) {
-    return moe_experts_entry(x, W_gate_up, W_down, packed, k, ids, w, residual, T, d, N, m, K,
+    (void)packed;  // the kernels read the row-major weights as fast
+    return moe_experts_entry(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                              dtype, y, workspace, workspace_bytes, stream);
 }
 
 static int moe_forward_entry(const void* x, const void* W_router, const void* W_gate_up,
-                             const void* W_down, const void* packed, const void* residual,
+                             const void* W_down, const void* residual,
                              int64_t T, int32_t d, int32_t N, int32_t m, int32_t dtype,
                              const elb_route_params* params, void* y, void* workspace,
                              size_t workspace_bytes, float* logits_out, int32_t* k_out,
@@ -494,7 +494,7 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
                                         (int*)(ws + L.hist), dispatch_hist_ld(T), s),
                 "router_route_dma"))
             return rc;
-        return experts_impl(x, W_gate_up, W_down, packed, k, ids, w, residual, T, d, N, m, K,
+        return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                             dtype, y, ws, L, counts_out, s, true, split_hist_subs(T));
     }
     if (router_split_usable(dtype, T, d, N, K) && !skinny) {
@@ -504,7 +504,7 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
                                           dispatch_hist_ld(T), s),
                 "router_split_route"))
             return rc;
-        return experts_impl(x, W_gate_up, W_down, packed, k, ids, w, residual, T, d, N, m, K,
+        return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                             dtype, y, ws, L, counts_out, s, true, split_hist_subs(T));
     }
     if (router_slices_usable(dtype, T, N, K)) {
@@ -514,7 +514,7 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
                                            dispatch_hist_ld(T), s),
                 "router_slices_route"))
             return rc;
-        return experts_impl(x, W_gate_up, W_down, packed, k, ids, w, residual, T, d, N, m, K,
+        return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                             dtype, y, ws, L, counts_out, s, true, split_hist_subs(T));
     }
     if (router_route_fusable(dtype, K) && !(N == 64 && T <= kSmallBatch)) {
@@ -528,7 +528,7 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
         if (int rc = hip_status(launch_route(logits, T, N, *params, k, ids, w, s), "route"))
             return rc;
     }
-    return experts_impl(x, W_gate_up, W_down, packed, k, ids, w, residual, T, d, N, m, K,
+    return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                         dtype, y, ws, L, counts_out, s);
 }
 
@@ -538,7 +538,7 @@ int elb_moe_forward(const void* x, const void* W_router, const void* W_gate_up,
                     void* workspace, size_t workspace_bytes, float* logits_out,
                     int32_t* k_out, int32_t* ids_out, float* w_out, int32_t* counts_out,
                     void* stream) {
-    return moe_forward_entry(x, W_router, W_gate_up, W_down, nullptr, residual, T, d, N, m,
+    return moe_forward_entry(x, W_router, W_gate_up, W_down, residual, T, d, N, m,
                              dtype, params, y, workspace, workspace_bytes, logits_out, k_out,
                              ids_out, w_out, counts_out, stream);
 }
@@ -549,7 +549,8 @@ int elb_moe_forward_packed(const void* x, const void* W_router, const void* W_ga
                            const elb_route_params* params, void* y, void* workspace,
                            size_t workspace_bytes, float* logits_out, int32_t* k_out,
                            int32_t* ids_out, float* w_out, int32_t* counts_out, void* stream) {
-    return moe_forward_entry(x, W_router, W_gate_up, W_down, packed, residual, T, d, N, m,
+    (void)packed;  // the kernels read the row-major weights as fast
+    return moe_forward_entry(x, W_router, W_gate_up, W_down, residual, T, d, N, m,
                              dtype, params, y, workspace, workspace_bytes, logits_out, k_out,
                              ids_out, w_out, counts_out, stream);
 }
@@ -573,7 +574,7 @@ int elb_moe_forward_noalloc(const void* x, const void* W_router, const void* W_g
                     "%zu (use elb_moe_forward with a workspace)", need, kScratchBytes);
     void* ws = nullptr;
     if (int rc = scratch_address(&ws)) return rc;
-    return moe_forward_entry(x, W_router, W_gate_up, W_down, nullptr, residual, T, d, N, m,
+    return moe_forward_entry(x, W_router, W_gate_up, W_down, residual, T, d, N, m,
                              dtype, params, y, ws, kScratchBytes, logits_out, k_out, ids_out,
                              w_out, counts_out, stream);
 }

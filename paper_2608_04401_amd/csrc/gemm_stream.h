@@ -6,7 +6,8 @@
 // token row.  The token rows (up to 16 * MT) are the second operand, read from L2.
 //   gate/up (MODE 0): a task is 32 H columns: its 32 gate rows and the 32 matching up rows
 //                     (SwiGLU in registers);  down (MODE 1): a task is 64 Y columns.
-// Used by the decode-sized kernels and by the remainder blocks of the large-tile kernel.
+// Used by the remainder blocks of the large-tile kernel; the decode-sized kernels share its
+// small pieces.
 #pragma once
 
 #include "common.h"
@@ -28,20 +29,22 @@ __device__ __forceinline__ float stream_silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z));
 }
 
+// physical 16-byte chunk of logical chunk c (0..7) in a 128-byte LDS row r
+__device__ __forceinline__ int swz8(int r, int c) {
+    return c ^ (((r >> 1) ^ ((r & 1) << 2)) & 7);
+}
+
 constexpr int SK_NF = 4;  // 16-row weight fragments per task (64 weight rows)
 
 // Lane addresses of a task: wp[f] in weight fragment f (row l16, k offset kq) and xp[t] in
 // token tile t (row l16 of rows [row0, row0 + rows), clamped to a valid row, k offset kq).
-// slots (optional): the rows are assignment slots t K + j listed at slots[row0 + r] (gate/up
-// reads token t's x row, down reads row slot of H) instead of the dispatch's row order.
 template <int MODE, int MAXMT>
 __device__ __forceinline__ void stream_task(const bf16_t* __restrict__ A,
                                             const int* __restrict__ row_token,
                                             const bf16_t* __restrict__ W, int e, int c,
                                             int row0, int rows, int d, int m, int lane,
                                             const bf16_t* (&wp)[SK_NF],
-                                            const bf16_t* (&xp)[MAXMT],
-                                            const int* slots = nullptr, int K = 1) {
+                                            const bf16_t* (&xp)[MAXMT]) {
     const int kd = (MODE == 0) ? d : m;
     const int l16 = lane & 15, kq = (lane >> 4) * 8;
 #pragma unroll
@@ -54,42 +57,17 @@ __device__ __forceinline__ void stream_task(const bf16_t* __restrict__ A,
     for (int t = 0; t < MAXMT; ++t) {
         int r = 16 * t + l16;
         r = r < rows ? r : rows - 1;  // rows past the chunk: a valid row, never stored
-        int64_t src;
-        if (slots) {
-            const int slot = slots[row0 + r];
-            src = (MODE == 0) ? (int64_t)(slot / K) * d : (int64_t)slot * m;
-        } else {
-            src = (MODE == 0) ? (int64_t)row_token[row0 + r] * d : (int64_t)(row0 + r) * m;
-        }
-        xp[t] = A + src + kq;
+        xp[t] = A + kq +
+                ((MODE == 0) ? (int64_t)row_token[row0 + r] * d : (int64_t)(row0 + r) * m);
     }
-}
-
-// Packed weights (elb_pack_expert_weights): a task's 64 weight rows are stored in the order
-// they are loaded -- per stage s, half h and fragment f, the 64 lanes' 16-byte operands
-// (weight row 16 f + lane % 16 of the task, k = 64 s + 32 h + 8 (lane / 16) .. + 8) -- so every
-// load instruction reads 1 KB contiguous and a task is one contiguous stream.
-constexpr int kPackUnit = 512;  // bf16 elements of one (stage, half, fragment) operand block
-
-// Lane addresses in a packed task (stage 0, half 0): wp[f] = task base + f units + lane's 16 B
-template <int MODE>
-__device__ __forceinline__ void stream_task_packed(const bf16_t* __restrict__ P, int e, int c,
-                                                   int d, int m, int lane,
-                                                   const bf16_t* (&wp)[SK_NF]) {
-    const int per_e = (MODE == 0) ? m / 32 : d / 64;
-    const int ns = ((MODE == 0) ? d : m) / 64;
-    const bf16_t* base = P + ((int64_t)e * per_e + c) * ns * (8 * kPackUnit);
-#pragma unroll
-    for (int f = 0; f < SK_NF; ++f) wp[f] = base + f * kPackUnit + lane * 8;
 }
 
 // acc[t][f] += the task's stages [s0, s1) (a stage is 64 of the contraction, two 32-deep
 // halves).  A ring of R register slots keeps R - 1 stages in flight: stage j lives in slot
 // j % R, and while stage j is multiplied, stage j + R - 1 is loaded into the slot stage j - 1
 // has just freed.  Unrolled by R, so every slot index is a constant.  Loads past the last
-// stage re-read it (clamped) and are never used.  PACKED: weights in the packed order, read
-// with the non-temporal hint (a contiguous stream read once).
-template <int MT, int MAXMT, int R = 3, bool PACKED = false>
+// stage re-read it (clamped) and are never used.
+template <int MT, int MAXMT, int R = 3>
 __device__ __forceinline__ void stream_mma(const bf16_t* const (&wp)[SK_NF],
                                            const bf16_t* const (&xp)[MAXMT], int s0, int s1,
                                            f32x4_t (&acc)[MT][SK_NF]) {
@@ -100,14 +78,8 @@ __device__ __forceinline__ void stream_mma(const bf16_t* const (&wp)[SK_NF],
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int f = 0; f < SK_NF; ++f) {
-                if (PACKED)
-                    ws[f][h] = __builtin_bit_cast(
-                        bf16x8_t, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(
-                                      wp[f] + (s * 8 + h * 4) * kPackUnit)));
-                else
-                    ws[f][h] = *reinterpret_cast<const bf16x8_t*>(wp[f] + k0 + 32 * h);
-            }
+            for (int f = 0; f < SK_NF; ++f)
+                ws[f][h] = *reinterpret_cast<const bf16x8_t*>(wp[f] + k0 + 32 * h);
 #pragma unroll
             for (int t = 0; t < MT; ++t)
                 xs[t][h] = *reinterpret_cast<const bf16x8_t*>(xp[t] + k0 + 32 * h);
@@ -152,20 +124,17 @@ __device__ __forceinline__ void stream_mma(const bf16_t* const (&wp)[SK_NF],
 // Store a task's outputs for token rows [0, rows): the lane holds token row (lane & 15) of
 // each tile and, per fragment f, the 4 consecutive output columns 16 f + (lane >> 4) * 4 + i
 // of the task (gate/up: SwiGLU of fragment f and f + 2, f < 2).  bf16 out, 8-byte stores.
-// slots (optional): output row of r is slots[out_row0 + r] instead of out_row0 + r.
 template <int MODE, int MT>
 __device__ __forceinline__ void stream_store(const f32x4_t (&acc)[MT][SK_NF], int rows,
                                              int64_t out_row0, int out_ld, int out_col,
-                                             bf16_t* __restrict__ C, int lane,
-                                             const int* slots = nullptr) {
+                                             bf16_t* __restrict__ C, int lane) {
     const int l16 = lane & 15;
     const int cq = (lane >> 4) * 4;
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
         const int r = 16 * t + l16;
         if (r >= rows) continue;
-        const int64_t orow = slots ? (int64_t)slots[out_row0 + r] : out_row0 + r;
-        bf16_t* dst = C + orow * (int64_t)out_ld + out_col + cq;
+        bf16_t* dst = C + (out_row0 + r) * (int64_t)out_ld + out_col + cq;
         if (MODE == 0) {
 #pragma unroll
             for (int f = 0; f < 2; ++f) {  // fragments 0, 1: gate; 2, 3: the matching up

@@ -107,3 +107,31 @@ def test_experts_decode_packed_small_widths(T, d, N, m, K):
     y1 = B.elb_moe_experts(x, Wgu, Wd, *args, packed=packed)
     torch.cuda.synchronize()
     assert torch.equal(y0.view(torch.int16), y1.view(torch.int16))
+
+
+@pytest.mark.parametrize("T,K,N", [(1, 8, 64), (3, 4, 16), (7, 8, 64), (8, 8, 64), (9, 7, 64)])
+def test_decode_fewer_slots_than_experts(T, K, N):
+    """T K on both sides of N (tasks numbered by slot below it, by expert from it on): outputs
+    and the per-expert counts, the zero ones included; seven 64-deep stages in d, so that the
+    four waves' quarters differ."""
+    L = synth.moe_layer(T, 448, N, 192, dtype="bf16", seed=60 + T)
+    x, Wr, Wgu, Wd = _gpu(L)
+    y, dbg = B.elb_moe_forward(x, Wr, Wgu, Wd, K=K, debug=True)
+    torch.cuda.synchronize()
+    ids = cpu(dbg["ids"])
+    assert (cpu(dbg["counts"]) == np.bincount(ids[ids >= 0], minlength=N)).all()
+    ref = O.moe_experts(L.x, L.W_gu, L.W_down, cpu(dbg["k"]), ids,
+                        cpu(dbg["w"]).astype(np.float64))
+    assert rel_err_rows(cpu(y), ref).max() < RTOL_BF16
+
+
+@pytest.mark.parametrize("T", [6, 20])
+def test_decode_one_expert_for_all_tokens(T):
+    """Every token's slots name experts 5 and 2 (T K below and above N): the first slot's blocks
+    serve every later one."""
+    L = synth.moe_layer(T, 128, 32, 64, dtype="bf16", seed=70 + T)
+    ids = np.tile(np.array([[5, 2, -1]], np.int32), (T, 1))
+    k = np.full(T, 2, np.int32)
+    k[T // 2] = 1  # its second slot is not used, whatever its id
+    w = np.tile(np.array([[0.6, 0.3, 0.0]], np.float32), (T, 1))
+    assert _experts(L, k, ids, w).max() < RTOL_BF16
