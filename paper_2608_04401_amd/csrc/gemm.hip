@@ -10,16 +10,14 @@
 // the grid is launched with an upper bound of M-tiles and surplus blocks exit at once.
 //
 // Kernels (all fp32 accumulation; the launchers at the end pick one per problem):
-//  - gemm_bf16_dma: the prefill kernel (on average at least 96 rows per expert).  Block tile
+//  - gemm_bf16_dma: the prefill kernel (gemm_tile_rows: at least 112 rows per expert).  Block tile
 //    256 x 256 x 64, 4 waves of 128 x 128 on v_mfma_f32_32x32x16_bf16, operands copied
 //    global -> LDS by global_load_lds_dwordx4 into a 5-unit ring; remainder rows of a few
 //    experts (TilePlan) go to extra blocks of the same launch (weight-streaming tasks of
 //    gemm_stream.h).  Described in detail above the kernel.
-//  - gemm_bf16: smaller problems.  v_mfma_f32_16x16x32_bf16, block tile 128 x 128 x 64,
-//    4 waves (2 x 2) of 64 x 64, LDS double buffered with register prefetch, rows padded by
-//    8 bf16 so that 16 lanes reading 16-byte fragments of 16 consecutive rows hit distinct
-//    banks.  In gate_up the 128 B-tile columns are 64 gate and the matching 64 up columns,
-//    and each wave owns matching gate/up 16-column pairs, so SwiGLU is applied in registers.
+//  - gemm_bf16_mid: smaller problems.  Block tile 64 or 128 x 128 x 64, two blocks per CU,
+//    operands copied global -> LDS likewise, the contraction started at a different k-tile in
+//    each N-tile.  Described above the kernel.
 //  - decode-sized batches use gemm_skinny.hip instead (weight streaming).
 // fp32 path: plain VALU FMA tiles (64 x 64 x 16), for the fp32 configuration.
 #include "gemm_stream.h"
@@ -66,157 +64,265 @@ __device__ __forceinline__ float silu(float z) {
 }
 
 // ------------------------------------------------------------------------------------------
-// bf16 MFMA kernel
+// bf16 MFMA kernel for mid-sized batches (tens of rows per expert): 64 or 128 x 128 block tiles
+//
+// Here the expert weights still have to be streamed (at 60 rows per expert the MFMAs need a
+// third of the time the weights take), but every weight meets too many token rows for the
+// decode kernels, which read the rows straight from L2.  So both operands go through LDS
+// (global_load_lds_dwordx4, 8 rows x 128 bytes per instruction, chunks XOR-swizzled as in the
+// large-tile kernel), and everything else is arranged for the stream:
+//  - 80 KB of LDS per block, two blocks per CU: one block's start, end and barriers fall into
+//    the other's stream;
+//  - three 64-deep weight units of 128 rows (16 KB), and two (128-row tiles) or three (64-row
+//    tiles) token units: a unit is refilled as soon as the barrier shows that every wave has
+//    read it, so weights are two k-tiles ahead;
+//  - block (e, ntile) starts its contraction at k-tile ntile nk / nt_count and wraps around:
+//    weight rows lie a multiple of 1 KB or more apart, and blocks that all walk the same
+//    columns at the same time crowd onto part of the memory channels (gate/up at 60 rows per
+//    expert, the former register-staged form of this kernel: 135 us in step, 107 us rotated);
+//  - the M-tiles of an expert that share a weight tile are neighbours on one XCD and start at
+//    the same k-tile, so the second one finds most of the weights in L2.  Weights that only
+//    one tile reads carry the non-temporal hint, shared ones do not (two tiles per expert, 152
+//    rows: gate/up 213 us with the hint, 153 without; one tile, 60 rows: 96 and 102).
+// A tile with at most 64 rows left takes the 64-row form (block-uniform): half the LDS traffic
+// and MFMAs.  4 waves (2 x 2), v_mfma_f32_32x32x16_bf16 with the weights first, so a lane ends
+// with 4 consecutive output columns of a token row; in gate/up the 128 weight rows are 64 gate
+// and the matching 64 up rows, and each wave owns matching 32-column pairs.
+// Measured against the register-staged double-buffered form it replaces (OLMoE-shaped layer,
+// gate/up + down us): 256 tokens 130 + 56 -> 85 + 47, 512 tokens 135 + 63 -> 93 + 52 (5.8 and
+// 5.1 TB/s of weights).
 // ------------------------------------------------------------------------------------------
-constexpr int BM = 128, BN = 128, BK = 64, LDK = BK + 8;
+constexpr int BM = 128, BN = 128;
 
-template <int MODE>  // 0 = gate_up (+SwiGLU -> H), 1 = down (-> Y)
-__global__ __launch_bounds__(256) void gemm_bf16(const bf16_t* __restrict__ A,
-                                                 const int* __restrict__ row_token,
-                                                 const bf16_t* __restrict__ B,
-                                                 const int* __restrict__ offsets,
-                                                 const int* __restrict__ tile_off, int N, int d,
-                                                 int m, bf16_t* __restrict__ C) {
-    __shared__ __attribute__((aligned(16))) bf16_t As[2][BM][LDK];
-    __shared__ __attribute__((aligned(16))) bf16_t Bs[2][BN][LDK];
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-    const int nt_count = (MODE == 0) ? m / 64 : (d + BN - 1) / BN;
-    int tile, ntile;
-    if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
-    int e, row0, rows;
-    find_tile(tile_off, offsets, N, tile, BM, e, row0, rows);
+// two floats -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32
+typedef __bf16 bf16x2_vt __attribute__((ext_vector_type(2)));
+typedef float f32x2_vt __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+    const f32x2_vt v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_vt));
+}
 
+// MODE 0 = gate_up (+SwiGLU -> H), 1 = down (-> Y); TM: rows of the block tile (64 or 128)
+template <int MODE, int TM>
+__device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
+                                              const int* __restrict__ row_token,
+                                              const bf16_t* __restrict__ B, int e, int row0,
+                                              int rows, int ntile, int nt_count, int d, int m,
+                                              bf16_t* __restrict__ C, char* sm, bool nt) {
+    constexpr int TK = 64;
+    constexpr int BU = BN * TK * 2, AU = TM * TK * 2;  // bytes of a weight / token unit
+    constexpr int NB = 3, NA = (TM == 64) ? 3 : 2;     // units of each
+    constexpr int IB = BN / 32, IA = TM / 32;          // copy instructions per wave and unit
+    constexpr int FM = TM / 64;                        // 32-row token fragments per wave
+    constexpr int OUTC = (MODE == 0) ? BN / 2 : BN;    // output columns of the block
+    constexpr int PITCH = OUTC * 2 + 16;               // bytes per row of the staged output
+    static_assert(NB * BU + NA * AU <= 5 * 128 * 128 && TM * PITCH <= 5 * 128 * 128, "LDS");
+    char* const smb = sm;
+    char* const sma = sm + NB * BU;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wid = tid >> 6;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wid >> 1, wn = wid & 1;
-
-    // K dimension of this GEMM and the row stride of A / B
     const int Kd = (MODE == 0) ? d : m;
-    // per-thread global source rows for the 4 A chunks and 4 B chunks it loads
-    const bf16_t* a_src[4];
-    const bf16_t* b_src[4];
-    int kc8[4];
+    const int nk = Kd / TK;
+    const int rot = (int)((int64_t)ntile * nk / nt_count);  // first k-tile, < nk
+
+    // copy sources: lane l of copy i fills physical chunk l & 7 of the unit's row
+    // 8 (I wid + i) + (l >> 3) with that row's logical chunk (64-bit addresses)
+    const char* a_src[IA];
+    const char* b_src[IB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = tid + 256 * i;
-        const int r = c >> 3;
-        kc8[i] = (c & 7) * 8;
-        const int rr = r < rows ? r : rows - 1;  // rows past the expert's end: clamp, unused
+    for (int i = 0; i < IA; ++i) {
+        const int r = 8 * (IA * wid + i) + (lane >> 3);
+        const int rr = r < rows ? r : rows - 1;  // rows past the tile's end: never stored
+        const int64_t src = (MODE == 0) ? (int64_t)row_token[row0 + rr] * d
+                                        : (int64_t)(row0 + rr) * m;
+        a_src[i] = reinterpret_cast<const char*>(A + src) + swz8(r, lane & 7) * 16;
+    }
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+        const int r = 8 * (IB * wid + i) + (lane >> 3);
+        int brow;
         if (MODE == 0) {
-            const int tok = row_token[row0 + rr];
-            a_src[i] = A + (int64_t)tok * d;
-            const int hc = ntile * 64;  // first H column of this tile
-            const int brow = (r < 64) ? (hc + r) : (m + hc + (r - 64));
-            b_src[i] = B + ((int64_t)e * 2 * m + brow) * d;
+            brow = (r < 64) ? ntile * 64 + r : m + ntile * 64 + (r - 64);
         } else {
-            a_src[i] = A + (int64_t)(row0 + rr) * m;
-            int brow = ntile * BN + r;
-            brow = brow < d ? brow : d - 1;
-            b_src[i] = B + ((int64_t)e * d + brow) * m;
+            brow = ntile * BN + r;
+            brow = brow < d ? brow : d - 1;  // columns past d: never stored
         }
+        const int64_t src = ((int64_t)e * ((MODE == 0) ? 2 * m : d) + brow) * Kd;
+        b_src[i] = reinterpret_cast<const char*>(B + src) + swz8(r, lane & 7) * 16;
+    }
+    const uint32_t lds_b = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uintptr_t)(lds_void_t*)smb + (uint32_t)wid * (IB * 1024));
+    const uint32_t lds_a = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uintptr_t)(lds_void_t*)sma + (uint32_t)wid * (IA * 1024));
+    // The copies are inline assembly: the compiler cannot tell which unit a copy writes, and
+    // would otherwise wait for every copy in flight before each LDS read; waits are explicit.
+    auto k_bytes = [&](int t) {  // byte offset of k-tile t of this block's rotated order
+        const int kt = t + rot < nk ? t + rot : t + rot - nk;
+        return (int64_t)kt * (TK * 2);
+    };
+    auto issue_a = [&](int t, int unit) {
+        const int64_t kb = k_bytes(t);
+#pragma unroll
+        for (int i = 0; i < IA; ++i) {
+            const uint32_t la = lds_a + unit * AU + i * 1024;
+            const char* const va = a_src[i] + kb;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :: "s"(la), "v"(va) : "memory", "m0");
+        }
+    };
+    auto issue_b = [&](int t, int unit) {
+        const int64_t kb = k_bytes(t);
+#pragma unroll
+        for (int i = 0; i < IB; ++i) {
+            const uint32_t la = lds_b + unit * BU + i * 1024;
+            const char* const va = b_src[i] + kb;
+            if (nt)
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                             :: "s"(la), "v"(va) : "memory", "m0");
+            else
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+                             :: "s"(la), "v"(va) : "memory", "m0");
+        }
+    };
+
+    const int l32 = lane & 31, hi = lane >> 5;
+    int a_row[FM], b_row[2];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) a_row[i] = (wm * (TM / 2) + 32 * i + l32) * 128;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        b_row[i] = ((MODE == 0 ? 64 * i + 32 * wn : 64 * wn + 32 * i) + l32) * 128;
+    int cofs[4];  // byte offset of the chunk this lane reads for k16-step kk
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) cofs[kk] = swz8(l32, 2 * kk + hi) * 16;
+
+    f32x16_t acc[FM][2];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+
+    // Copies in flight: at the barrier that opens k-tile t every wave has read tile t - 1, whose
+    // units then receive the weights of tile t + 2 and the token rows of tile t + 2 (three
+    // token units) or t + 1 (two).  Copies complete in order, and what tile t + 1 needs is
+    // issued before the weights of t + 2, so the wait that opens it may leave those IB (three
+    // token units: IB + IA) copies in flight.
+    constexpr int AHEAD_A = NA - 1;
+    if (AHEAD_A == 2) {
+        issue_a(0, 0);
+        issue_b(0, 0);
+        if (nk > 1) {
+            issue_a(1, 1);
+            issue_b(1, 1);
+        }
+    } else {
+        issue_b(0, 0);
+        issue_a(0, 0);
+        if (nk > 1) issue_b(1, 1);
+    }
+    int ub = 0, ua = 0;  // units of tile t
+    for (int t = 0; t < nk; ++t) {
+        if (t + 1 < nk) ELB_WAIT_VMCNT(AHEAD_A == 2 ? IB + IA : IB);
+        else ELB_WAIT_VMCNT(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const int ua_next = ua + AHEAD_A >= NA ? ua + AHEAD_A - NA : ua + AHEAD_A;
+        const int ub_next = ub + 2 >= NB ? ub + 2 - NB : ub + 2;
+        if (t + AHEAD_A < nk) issue_a(t + AHEAD_A, ua_next);
+        if (t + 2 < nk) issue_b(t + 2, ub_next);
+        const char* const pa = sma + ua * AU;
+        const char* const pb = smb + ub * BU;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            bf16x8_t fa[FM], fb[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                fb[i] = *reinterpret_cast<const bf16x8_t*>(pb + b_row[i] + cofs[kk]);
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+                fa[i] = *reinterpret_cast<const bf16x8_t*>(pa + a_row[i] + cofs[kk]);
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i],
+                                                                        acc[i][j], 0, 0, 0);
+        }
+        ua = ua + 1 == NA ? 0 : ua + 1;
+        ub = ub + 1 == NB ? 0 : ub + 1;
     }
 
-    f32x4_t acc[4][4];
+    // epilogue: bf16 rows staged in LDS (lane: token row l32, columns 8 g + 4 hi .. + 3 of each
+    // 32-column fragment), then whole rows stored with 16-byte stores
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FM; ++i) {
+        char* const rowp = sm + (wm * (TM / 2) + 32 * i + l32) * PITCH + hi * 8;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    // B-tile row read by fragment ni of this wave (lane row l16 added by the caller)
-    int brow_base[4];
+        for (int j = 0; j < ((MODE == 0) ? 1 : 2); ++j)
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
-        brow_base[ni] = (MODE == 0) ? ((ni < 2) ? (wn * 32 + ni * 16) : (64 + wn * 32 + (ni - 2) * 16))
-                                    : (wn * 64 + ni * 16);
-
-    u32x4_t ra[4], rb[4];
-    const int nk = Kd / BK;
+            for (int g = 0; g < 4; ++g) {
+                float v[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        ra[i] = *reinterpret_cast<const u32x4_t*>(a_src[i] + kc8[i]);
-        rb[i] = *reinterpret_cast<const u32x4_t*>(b_src[i] + kc8[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = (tid + 256 * i) >> 3;
-        *reinterpret_cast<u32x4_t*>(&As[0][r][kc8[i]]) = ra[i];
-        *reinterpret_cast<u32x4_t*>(&Bs[0][r][kc8[i]]) = rb[i];
+                for (int r = 0; r < 4; ++r) {
+                    const float a0 = acc[i][j][4 * g + r];
+                    v[r] = (MODE == 0) ? silu(a0) * acc[i][1][4 * g + r] : a0;
+                }
+                const int col = ((MODE == 0) ? wn * 32 : wn * 64 + j * 32) + g * 8;
+                const u32x2_t pk = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+                *reinterpret_cast<u32x2_t*>(rowp + col * 2) = pk;
+            }
     }
     __syncthreads();
-    const int l16 = lane & 15;
-    const int kq = (lane >> 4) * 8;
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        const bool more = kt + 1 < nk;
-        if (more) {
-            const int k0 = (kt + 1) * BK;
+    constexpr int CPR = OUTC * 2 / 16;  // 16-byte chunks per row
+    constexpr int RPI = 256 / CPR;      // rows per pass of the block
+    const int cc = tid % CPR, r0 = tid / CPR;
+    const int ldc = (MODE == 0) ? m : d;
+    const int col = ntile * OUTC + cc * 8;
+    if (MODE == 1 && col >= d) return;
+    bf16_t* const dst = C + (int64_t)row0 * ldc + col;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                ra[i] = *reinterpret_cast<const u32x4_t*>(a_src[i] + k0 + kc8[i]);
-                rb[i] = *reinterpret_cast<const u32x4_t*>(b_src[i] + k0 + kc8[i]);
-            }
-        }
-#pragma unroll
-        for (int ks = 0; ks < BK / 32; ++ks) {
-            bf16x8_t af[4], bfr[4];
-#pragma unroll
-            for (int mi = 0; mi < 4; ++mi)
-                af[mi] = *reinterpret_cast<const bf16x8_t*>(&As[buf][wm * 64 + mi * 16 + l16][ks * 32 + kq]);
-#pragma unroll
-            for (int ni = 0; ni < 4; ++ni)
-                bfr[ni] = *reinterpret_cast<const bf16x8_t*>(&Bs[buf][brow_base[ni] + l16][ks * 32 + kq]);
-#pragma unroll
-            for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < 4; ++ni)
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[mi], bfr[ni], acc[mi][ni], 0, 0, 0);
-        }
-        if (more) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int r = (tid + 256 * i) >> 3;
-                *reinterpret_cast<u32x4_t*>(&As[buf ^ 1][r][kc8[i]]) = ra[i];
-                *reinterpret_cast<u32x4_t*>(&Bs[buf ^ 1][r][kc8[i]]) = rb[i];
-            }
-        }
-        __syncthreads();
+    for (int b = 0; b < TM / RPI; ++b) {
+        const int r = r0 + b * RPI;
+        if (r < rows)
+            *reinterpret_cast<u32x4_t*>(dst + (int64_t)r * ldc) =
+                *reinterpret_cast<const u32x4_t*>(sm + r * PITCH + cc * 16);
     }
+}
 
-    // epilogue: lane holds rows (lane>>4)*4 + r, column lane&15 of each 16x16 fragment
-    const int rq = (lane >> 4) * 4;
-    if (MODE == 0) {
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int lr = wm * 64 + mi * 16 + rq + r;
-                if (lr < rows) {
-                    bf16_t* dst = C + (int64_t)(row0 + lr) * m + ntile * 64 + wn * 32 + l16;
-#pragma unroll
-                    for (int ni = 0; ni < 2; ++ni) {
-                        const float g = acc[mi][ni][r];
-                        const float u = acc[mi][ni + 2][r];
-                        dst[ni * 16] = f32_to_bf16(silu(g) * u);
-                    }
-                }
-            }
-    } else {
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int lr = wm * 64 + mi * 16 + rq + r;
-                if (lr < rows) {
-                    bf16_t* dst = C + (int64_t)(row0 + lr) * d;
-#pragma unroll
-                    for (int ni = 0; ni < 4; ++ni) {
-                        const int col = ntile * BN + wn * 64 + ni * 16 + l16;
-                        if (col < d) dst[col] = f32_to_bf16(acc[mi][ni][r]);
-                    }
-                }
-            }
+template <int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_mid(
+    const bf16_t* __restrict__ A, const int* __restrict__ row_token,
+    const bf16_t* __restrict__ B, const int* __restrict__ offsets,
+    const int* __restrict__ tile_off, int N, int d, int m, bf16_t* __restrict__ C) {
+    __shared__ __attribute__((aligned(1024))) char sm[5 * 128 * 128];
+    const int nt_count = (MODE == 0) ? m / 64 : (d + BN - 1) / BN;
+    // block -> (expert, N-tile, M-tile innermost), XCD-contiguous (xcd_tile with one column)
+    int L, unused;
+    if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, 1, L, unused)) return;
+    int lo = 0, hi = N - 1;  // largest e with tile_off[e] nt_count <= L
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (tile_off[mid] * nt_count <= L) lo = mid;
+        else hi = mid - 1;
     }
+    const int e = lo;
+    const int tiles = tile_off[e + 1] - tile_off[e];
+    const int local = L - tile_off[e] * nt_count;
+    const int ntile = local / tiles;
+    const int row0 = offsets[e] + (local - ntile * tiles) * BM;
+    const int left = offsets[e + 1] - row0;
+    if (left <= 64)
+        gemm_mid_body<MODE, 64>(A, row_token, B, e, row0, left, ntile, nt_count, d, m, C, sm, tiles == 1);
+    else
+        gemm_mid_body<MODE, 128>(A, row_token, B, e, row0, left < BM ? left : BM, ntile,
+                                 nt_count, d, m, C, sm, tiles == 1);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -242,18 +348,6 @@ __global__ __launch_bounds__(256) void gemm_bf16(const bf16_t* __restrict__ A,
 // row-major tile in LDS and the block then stores whole rows with 16-byte coalesced stores.
 // ------------------------------------------------------------------------------------------
 constexpr int LBM = 256, LBN = 256;
-
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-
-
-// two floats -> two bf16 (round to nearest even) in one v_cvt_pk_bf16_f32
-typedef __bf16 bf16x2_vt __attribute__((ext_vector_type(2)));
-typedef float f32x2_vt __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    const f32x2_vt v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_vt));
-}
 
 // Remainder rows of the large-tile GEMM (TilePlan): for each expert e in tail_list, the
 // 1..kTailRows rows past its last full M-tile, by extra blocks at the end of the grid, one per
@@ -708,9 +802,17 @@ int gemm_tile_rows(int dtype, int64_t T, int K, int N, int d, int m) {
     // the 128-row kernel, which addresses with 64-bit pointers
     const bool offsets_fit = (uint64_t)T * (uint64_t)d * 2u < ((uint64_t)1 << 32) &&
                              (uint64_t)m * (uint64_t)d * 4u < ((uint64_t)1 << 32);
-    // from about 96 rows per expert the 256-row tiles are faster (measured on the OLMoE-shaped
-    // layer: at 120 rows per expert gate/up 161 -> 140 us; at 60 rows the two are even)
-    return (m % 128 == 0 && d >= 128 && T > 0 && avg_rows >= 96 && offsets_fit) ? LBM : BM;
+    // Which tiles are faster, measured on whole layers (us, 128-row kernel / this one).
+    // Rows per expert, OLMoE-shaped: 98 179 / 227, 113 204 / 231, 128 231 / 231, 143 250 / 236;
+    // with d = 2560, m = 1536 at 120 rows 404 / 380.  From some 112 rows on many experts need two
+    // 128-row tiles, and the second pass over the weights costs what the finer tiles gain.
+    // Few large tiles leave compute units idle (one block each): about (T K + 128 N) / 256
+    // M-tiles times m / 128 blocks in gate/up.  90 blocks 46 / 66, 96 75 / 94, 120 48 / 66; at
+    // 157 and 160 58 / 69 and 111 / 98; at 216 and more within 5 % either way.  So this kernel
+    // needs more than 128 blocks, half of the compute units.
+    const int64_t blocks = (T * K + (int64_t)N * 128) / 256 * (m / 128);
+    return (m % 128 == 0 && d >= 128 && T > 0 && avg_rows >= 112 && blocks > 128 &&
+            offsets_fit) ? LBM : BM;
 }
 
 hipError_t launch_gemm_gate_up(const void* x, const void* Wgu, const int* row_token,
@@ -727,7 +829,7 @@ hipError_t launch_gemm_gate_up(const void* x, const void* Wgu, const int* row_to
                            tail_list, (int)big, N, d, m, (bf16_t*)H, (int)nt_weights);
     } else if (dtype == ELB_BF16) {
         ProfileScope prof("gemm_gate_up_bf16_s", s);
-        ELB_LAUNCH(gemm_bf16<0>, dim3(grid8(max_tiles * (m / 64))), dim3(256),
+        ELB_LAUNCH(gemm_bf16_mid<0>, dim3(grid8(max_tiles * (m / 64))), dim3(256),
                            0, s, (const bf16_t*)x, row_token, (const bf16_t*)Wgu, offsets,
                            tile_off, N, d, m, (bf16_t*)H);
     } else {
@@ -753,7 +855,7 @@ hipError_t launch_gemm_down(const void* H, const void* Wd, const int* offsets,
                            tile_off, tail_list, (int)big, N, d, m, (bf16_t*)Y, (int)nt_weights);
     } else if (dtype == ELB_BF16) {
         ProfileScope prof("gemm_down_bf16_s", s);
-        ELB_LAUNCH(gemm_bf16<1>, dim3(grid8(max_tiles * ((d + BN - 1) / BN))),
+        ELB_LAUNCH(gemm_bf16_mid<1>, dim3(grid8(max_tiles * ((d + BN - 1) / BN))),
                            dim3(256), 0, s, (const bf16_t*)H, (const int*)nullptr,
                            (const bf16_t*)Wd, offsets, tile_off, N, d, m, (bf16_t*)Y);
     } else {

@@ -1,0 +1,34 @@
+"""GPU parity of the mid-sized expert GEMM kernel (64- and 128-row tiles) at the edges of its
+tiles, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2608_04401_amd import binding as B
+from paper_2608_04401_amd import synth
+
+from helpers import RTOL_BF16, cpu, rel_err_rows, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,m", [(64, 64), (192, 64), (320, 192), (128, 128), (64, 576)])
+def test_mid_tile_edges(d, m):
+    """Experts with 0, 1, 63 .. 65, 127 .. 129, 192, 193 and 256 rows: both tile forms, one to
+    three tiles sharing their weights, one to nine k-tiles (started at every N-tile's own one),
+    a last N-tile of 64 of 128 columns (d = 64, 192, 320)."""
+    counts = [0, 1, 63, 64, 65, 127, 128, 129, 192, 193, 256]
+    N, T = len(counts), sum(counts)
+    L = synth.moe_layer(T, d, N, m, dtype="bf16", seed=d + m)
+    rng = np.random.default_rng(d)
+    ids = rng.permutation(np.repeat(np.arange(N), counts)).astype(np.int32)[:, None]
+    k = np.ones(T, np.int32)
+    w = rng.uniform(0.1, 1.0, (T, 1)).astype(np.float32)
+    x, Wgu, Wd = (to_gpu(a, torch.bfloat16) for a in (L.x, L.W_gu, L.W_down))
+    y = B.elb_moe_experts(x, Wgu, Wd, to_gpu(k, torch.int32), to_gpu(ids, torch.int32),
+                          to_gpu(w))
+    torch.cuda.synchronize()
+    ref = O.moe_experts(L.x, L.W_gu, L.W_down, k, ids, w.astype(np.float64))
+    # bf16 storage of H and of the expert output: two roundings of 2^-9 relative
+    assert rel_err_rows(cpu(y), ref).max() < RTOL_BF16
