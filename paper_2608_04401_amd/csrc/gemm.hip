@@ -564,15 +564,27 @@ __device__ __forceinline__ void gemm_dma_body(
     // t + 1's are those of B(t + 2), so the wait is vmcnt <= 8 (0 near the end).
     // A bare s_barrier, not __syncthreads(): the latter's fence would make the compiler drain
     // every copy in flight.
+    //
+    // Rotation: an expert with one M-tile has its weights read once, and the kernel waits on that
+    // stream; its odd N-tiles then start in the middle of the contraction and wrap around, so
+    // that blocks do not all walk the same columns of rows a multiple of 1 KB apart, i.e. the
+    // same part of the memory channels (OLMoE-shaped layer, us: 1024 tokens 239 -> 221, 1600
+    // tokens 250 -> 237, 1900 tokens 263 -> 257).  More starting points (4 or 8) cost part of
+    // that again from 1600 tokens on (245, 242): the N-tiles share the token rows through L2, and
+    // the rows of every point in use have to fit there.  With more M-tiles, where the weights are
+    // shared too, all blocks stay in step (4096 tokens with 8 points: 447 -> 466 us).
     const int nk = Kd / TK;  // >= 1
+    const bool alone = tile_off[e + 1] - tile_off[e] == 1;
+    const int rot = alone && (ntile & 1) ? nk / 2 : 0;
+    auto k_of = [&](int t) { return (t + rot < nk ? t + rot : t + rot - nk) * TK; };
     // as if barriers at t = -3, -2, -1 had issued B(0); A(0), B(1); A(1), B(2)
-    issue(Bblk, b_off, 0, 0, NTW);
-    issue(Ablk, a_off, 1, 0, false);
+    issue(Bblk, b_off, 0, k_of(0), NTW);
+    issue(Ablk, a_off, 1, k_of(0), false);
     if (nk > 1) {
-        issue(Bblk, b_off, 2, TK, NTW);
-        issue(Ablk, a_off, 3, TK, false);
+        issue(Bblk, b_off, 2, k_of(1), NTW);
+        issue(Ablk, a_off, 3, k_of(1), false);
         if (nk > 2) {
-            issue(Bblk, b_off, 4, 2 * TK, NTW);
+            issue(Bblk, b_off, 4, k_of(2), NTW);
             ELB_WAIT_VMCNT(24);
         } else {
             ELB_WAIT_VMCNT(16);
@@ -587,6 +599,8 @@ __device__ __forceinline__ void gemm_dma_body(
     for (; t < nk - 1; ++t) {
         const int ub1 = ub + 2 >= NU ? ub + 2 - NU : ub + 2;  // units of tile t + 1
         const int ua1 = ua + 2 >= NU ? ua + 2 - NU : ua + 2;
+        const int ka = __builtin_amdgcn_readfirstlane(k_of(t + 2));
+        const int kb = __builtin_amdgcn_readfirstlane(k_of(t + 3));
         load(fa1, fb1, ua, ub, 1);
         mma(fa0, fb0, true);
         load(fa0, fb0, ua, ub, 2);
@@ -616,9 +630,9 @@ __device__ __forceinline__ void gemm_dma_body(
             if ((q & 1) == 1) {
                 const int i = q >> 1;
                 if (i < 8) {
-                    if (t + 2 < nk) issue_one(Ablk, a_off, ub, (t + 2) * TK, false, i);  // -> unit 2t
+                    if (t + 2 < nk) issue_one(Ablk, a_off, ub, ka, false, i);  // -> unit 2t
                 } else {
-                    if (t + 3 < nk) issue_one(Bblk, b_off, ua, (t + 3) * TK, NTW, i - 8);
+                    if (t + 3 < nk) issue_one(Bblk, b_off, ua, kb, NTW, i - 8);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
