@@ -19,7 +19,7 @@
 //    operands copied global -> LDS likewise, the contraction started at a different k-tile in
 //    each N-tile.  Described above the kernel.
 //  - decode-sized batches use gemm_skinny.hip instead (weight streaming).
-// fp32 path: plain VALU FMA tiles (64 x 64 x 16), for the fp32 configuration.
+// fp32 path: gemm_f32, 64 x 64 x 32 tiles on the fp32 matrix instructions.
 #include "gemm_stream.h"
 
 namespace elb {
@@ -712,9 +712,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 VALU kernel: tile 64 x 64, k-step 16, 256 threads each computing 4 x 4 outputs
+// fp32 kernel: 64 x 64 block tile, k-tiles of 32 (128 bytes of a row), 4 waves (2 x 2) of
+// 32 x 32 on v_mfma_f32_16x16x4_f32 (fp32 products and sums; the weights first, so a lane ends
+// with 4 consecutive output columns of a token row)
+//
+// The matrix units bound it: 157 TFLOP/s nominal, twice the vector units' rate, against which
+// the LDS traffic of even this small tile is a quarter (16 KB copied and 32 KB read per k-tile
+// of 1024 matrix cycles).  So the tile is small, for the small layers that run in fp32: more
+// blocks to spread (three per CU), little padding.  Copies global -> LDS, three units deep, chunks
+// XOR-swizzled, as in the bf16 kernels.  An operand read is 16 bytes, four k of one row; the
+// four MFMAs of a 16-deep step each take one of the four from every lane, a permutation of the
+// contraction that both operands share.
+// Measured against 64 x 64 x 16 vector tiles (gate/up + down us): 1500 tokens, d = 1024, 16
+// experts, m = 528, K = 4: 236 + 105 -> 132 + 63; 2048 tokens, d = 1024, 32 experts, m = 640,
+// K = 8: 543 + 259 -> 333 + 168 (121 TFLOP/s without the padding in gate/up); the error against
+// 64 bits is the same (5.5e-8 and 4.2e-7 of the layer's output before and after).
 // ------------------------------------------------------------------------------------------
-constexpr int FBM = 64, FBN = 64, FBK = 16;
+constexpr int FBM = 64, FBN = 64, FBK = 32;
 
 template <int MODE>
 __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
@@ -723,82 +737,121 @@ __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
                                                 const int* __restrict__ offsets,
                                                 const int* __restrict__ tile_off, int N, int d,
                                                 int m, float* __restrict__ C) {
-    __shared__ float As[FBK][FBM + 4];
-    __shared__ float Bs[FBK][FBN + 4];
-    const int tile = blockIdx.x;
-    if (tile >= tile_off[N]) return;
+    constexpr int UNIT = 64 * FBK * 4, NU = 3;  // bytes of a unit (64 rows), units per operand
+    __shared__ __attribute__((aligned(1024))) char sm[2 * NU * UNIT];
+    const int nt_count = (MODE == 0) ? (m + 31) / 32 : (d + FBN - 1) / FBN;
+    int tile, ntile;
+    if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
     int e, row0, rows;
     find_tile(tile_off, offsets, N, tile, FBM, e, row0, rows);
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wid >> 1, wn = wid & 1;
     const int Kd = (MODE == 0) ? d : m;
     const int nout = (MODE == 0) ? m : d;  // output columns of this GEMM
+    const int nk = (Kd + FBK - 1) / FBK;
+    const bool half = Kd % FBK != 0;  // the last k-tile has 16 columns (d and m are % 16)
 
-    // loader: each thread loads one A element-quad and one B element-quad per k-step
-    const int lr = tid >> 2;        // 0..63: tile row (A) / tile column (B)
-    const int lk = (tid & 3) * 4;   // 0,4,8,12
-    const int rr = lr < rows ? lr : rows - 1;
-    const float* a_src;
-    if (MODE == 0) a_src = A + (int64_t)row_token[row0 + rr] * d;
-    else a_src = A + (int64_t)(row0 + rr) * m;
-    const float* b_src;
-    bool bvalid = true;
-    if (MODE == 0) {
-        const int hc = blockIdx.y * 32;
-        const int col = (lr < 32) ? hc + lr : hc + (lr - 32);
-        bvalid = col < m;
-        const int brow = (lr < 32) ? (bvalid ? col : 0) : m + (bvalid ? col : 0);
-        b_src = B + ((int64_t)e * 2 * m + brow) * d;
-    } else {
-        int brow = blockIdx.y * FBN + lr;
-        bvalid = brow < d;
-        b_src = B + ((int64_t)e * d + (bvalid ? brow : 0)) * m;
+    // copy sources: wave w copies rows [16 w, 16 w + 16) of each unit, 8 rows per instruction;
+    // lane l fills physical chunk l & 7 of row 8 i + (l >> 3) with that row's logical chunk (of
+    // a half k-tile: one of its four, the upper half is never read)
+    const char* a_src[2];
+    const char* b_src[2];
+    int chunk[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = 16 * wid + 8 * i + (lane >> 3);
+        chunk[i] = swz8(r, lane & 7) * 16;
+        const int rr = r < rows ? r : rows - 1;  // rows past the tile's end: never stored
+        const int64_t ar = (MODE == 0) ? (int64_t)row_token[row0 + rr] : (int64_t)(row0 + rr);
+        a_src[i] = reinterpret_cast<const char*>(A + ar * Kd);
+        int col = (MODE == 0) ? ntile * 32 + (r & 31) : ntile * FBN + r;
+        col = col < nout ? col : nout - 1;  // columns past the end: never stored
+        const int64_t br = (MODE == 0) ? (int64_t)e * 2 * m + (r < 32 ? col : m + col)
+                                       : (int64_t)e * d + col;
+        b_src[i] = reinterpret_cast<const char*>(B + br * Kd);
     }
-
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < Kd; k0 += FBK) {
-        const float4 av = *reinterpret_cast<const float4*>(a_src + k0 + lk);
-        const float4 bv = *reinterpret_cast<const float4*>(b_src + k0 + lk);
-        As[lk + 0][lr] = av.x; As[lk + 1][lr] = av.y; As[lk + 2][lr] = av.z; As[lk + 3][lr] = av.w;
-        Bs[lk + 0][lr] = bv.x; Bs[lk + 1][lr] = bv.y; Bs[lk + 2][lr] = bv.z; Bs[lk + 3][lr] = bv.w;
-        __syncthreads();
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uintptr_t)(lds_void_t*)sm + (uint32_t)wid * 2048);
+    auto issue = [&](int t, int unit) {
+        const int mask = half && t == nk - 1 ? 63 : 127;
 #pragma unroll
-        for (int kk = 0; kk < FBK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-            if (MODE == 0) {
-                b[0] = Bs[kk][tx * 2];
-                b[1] = Bs[kk][tx * 2 + 1];
-                b[2] = Bs[kk][32 + tx * 2];
-                b[3] = Bs[kk][32 + tx * 2 + 1];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t la = lds0 + (uint32_t)unit * UNIT + i * 1024;
+            const int64_t o = (int64_t)t * (FBK * 4) + (chunk[i] & mask);
+            const char* const va = a_src[i] + o;
+            const char* const vb = b_src[i] + o;
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :: "s"(la), "v"(va) : "memory", "m0");
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
+                         :: "s"(la + NU * UNIT), "v"(vb) : "memory", "m0");
         }
-        __syncthreads();
+    };
+
+    const int l16 = lane & 15, hq = lane >> 4;
+    int a_at[2], b_at[2], cofs[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        a_at[i] = (32 * wm + 16 * i + l16) * 128;
+        b_at[i] = NU * UNIT + ((MODE == 0 ? 32 * i + 16 * wn : 32 * wn + 16 * i) + l16) * 128;
+        cofs[i] = swz8(l16, 4 * i + hq) * 16;  // rows 16 apart swizzle alike
+    }
+    f32x4_t acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](const char* p, int ks) {
+        f32x4_t fa[2], fb[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            fa[i] = *reinterpret_cast<const f32x4_t*>(p + a_at[i] + cofs[ks]);
+            fb[i] = *reinterpret_cast<const f32x4_t*>(p + b_at[i] + cofs[ks]);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][c], fa[i][c],
+                                                                     acc[i][j], 0, 0, 0);
+    };
+
+    // at the barrier that opens k-tile t every wave has read tile t - 1, whose unit receives
+    // tile t + 2; the wait before it leaves tile t + 1's four copies in flight
+    const bool any = 32 * wm < rows;  // wave-uniform: a short tile's upper waves only copy
+    issue(0, 0);
+    if (nk > 1) issue(1, 1);
+    int u = 0;
+    for (int t = 0; t < nk; ++t) {
+        if (t + 1 < nk) ELB_WAIT_VMCNT(4);
+        else ELB_WAIT_VMCNT(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (t + 2 < nk) issue(t + 2, u + 2 >= NU ? u + 2 - NU : u + 2);
+        if (any) {
+            const char* const p = sm + u * UNIT;
+            step(p, 0);
+            if (!(half && t == nk - 1)) step(p, 1);
+        }
+        u = u + 1 == NU ? 0 : u + 1;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = ty * 4 + i;
+    for (int i = 0; i < 2; ++i) {
+        const int r = 32 * wm + 16 * i + l16;
         if (r >= rows) continue;
-        float* dst = C + (int64_t)(row0 + r) * nout;
+        float* const dst = C + (int64_t)(row0 + r) * nout;
         if (MODE == 0) {
+            const int col = ntile * 32 + 16 * wn + 4 * hq;
+            f32x4_t v;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int col = blockIdx.y * 32 + tx * 2 + j;
-                if (col < m) dst[col] = silu(acc[i][j]) * acc[i][j + 2];
-            }
+            for (int q = 0; q < 4; ++q) v[q] = silu(acc[i][0][q]) * acc[i][1][q];
+            if (col < nout) *reinterpret_cast<f32x4_t*>(dst + col) = v;
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int col = blockIdx.y * FBN + tx * 4 + j;
-                if (col < d) dst[col] = acc[i][j];
+            for (int j = 0; j < 2; ++j) {
+                const int col = ntile * FBN + 32 * wn + 16 * j + 4 * hq;
+                if (col < nout) *reinterpret_cast<f32x4_t*>(dst + col) = acc[i][j];
             }
         }
     }
@@ -848,8 +901,7 @@ hipError_t launch_gemm_gate_up(const void* x, const void* Wgu, const int* row_to
                            tile_off, N, d, m, (bf16_t*)H);
     } else {
         ProfileScope prof("gemm_gate_up_f32", s);
-        ELB_LAUNCH(gemm_f32<0>, dim3((unsigned)max_tiles, (unsigned)((m + 31) / 32)),
-                           dim3(256), 0, s, (const float*)x, row_token, (const float*)Wgu,
+        ELB_LAUNCH(gemm_f32<0>, dim3(grid8(max_tiles * ((m + 31) / 32))), dim3(256), 0, s, (const float*)x, row_token, (const float*)Wgu,
                            offsets, tile_off, N, d, m, (float*)H);
     }
     return hipGetLastError();
@@ -874,8 +926,7 @@ hipError_t launch_gemm_down(const void* H, const void* Wd, const int* offsets,
                            (const bf16_t*)Wd, offsets, tile_off, N, d, m, (bf16_t*)Y);
     } else {
         ProfileScope prof("gemm_down_f32", s);
-        ELB_LAUNCH(gemm_f32<1>, dim3((unsigned)max_tiles, (unsigned)((d + FBN - 1) / FBN)),
-                           dim3(256), 0, s, (const float*)H, (const int*)nullptr,
+        ELB_LAUNCH(gemm_f32<1>, dim3(grid8(max_tiles * ((d + FBN - 1) / FBN))), dim3(256), 0, s, (const float*)H, (const int*)nullptr,
                            (const float*)Wd, offsets, tile_off, N, d, m, (float*)Y);
     }
     return hipGetLastError();

@@ -7,7 +7,7 @@
 // blocks); each wave runs 4 v_mfma_f32_16x16x32_bf16 chains (16 experts each) with its loads
 // four steps ahead of their use, and the 4 partial 16 x N tiles are summed in LDS in order.
 // N <= 64, d % 32 == 0.
-// fp32: one thread per (token, expert) dot product (the small fp32 configuration).
+// fp32: one thread per (token, expert) dot product, operands through LDS (router_f32).
 #include "route_lane.h"
 
 namespace elb {
@@ -593,18 +593,70 @@ __global__ __launch_bounds__(256) void router_route_dma(
     }
 }
 
+// fp32 router: one block per (16 tokens, 16 experts), one thread per logit, which sums its d
+// products in order with one chain of fused multiply-adds.  Chunks of 128 columns of the 16
+// token rows and the 16 W_r rows go through LDS (the next chunk's loads are in flight in
+// registers meanwhile), so that memory is read in whole lines, once per block; rows padded by
+// 4 floats, so that the 16 rows of a 16-byte read fall in distinct banks.  VEC: 16-byte loads
+// (d % 4 == 0 and 16-byte aligned rows), else 4-byte ones.  The serial chain of d FMAs and
+// its LDS reads bounds it.
+// The same bits as, and at 1500 tokens, d = 1024, 16 experts 12 us against 123 us of, a thread
+// that walks its two rows in memory.
+constexpr int RFC = 128;  // columns per chunk
+template <bool VEC>
 __global__ __launch_bounds__(256) void router_f32(const float* __restrict__ x,
                                                   const float* __restrict__ Wr, int64_t T,
                                                   int d, int N, float* __restrict__ logits) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= T * N) return;
-    const int64_t t = i / N;
-    const int n = (int)(i - t * N);
-    const float* a = x + t * d;
-    const float* b = Wr + (int64_t)n * d;
+    __shared__ __attribute__((aligned(16))) float tile[2][16][RFC + 4];  // x rows, W_r rows
+    const int64_t t0 = (int64_t)blockIdx.x * 16;
+    const int n0 = (int)blockIdx.y * 16;
+    const int tid = threadIdx.x;
+    constexpr int W = VEC ? 4 : 1, PER = 16 * RFC / (256 * W);
+    typedef float vec_t __attribute__((ext_vector_type(W)));
+    vec_t v[2][PER];
+    // element q of this thread: row and column of the chunk; rows past T and experts past N
+    // re-read a valid row and give logits that are never written, columns past d are zero
+    auto load = [&](int c0) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int at = (tid + 256 * q) * W;
+            const int r = at / RFC, c = c0 + at % RFC;
+            const int64_t t = t0 + r < T ? t0 + r : T - 1;
+            const int n = n0 + r < N ? n0 + r : N - 1;
+            v[0][q] = v[1][q] = vec_t(0.f);
+            if (c < d) {
+                v[0][q] = *reinterpret_cast<const vec_t*>(x + t * d + c);
+                v[1][q] = *reinterpret_cast<const vec_t*>(Wr + (int64_t)n * d + c);
+            }
+        }
+    };
+    const int tr = tid >> 4, nl = tid & 15;
     float acc = 0.f;
-    for (int c = 0; c < d; ++c) acc = fmaf(a[c], b[c], acc);
-    logits[i] = acc;
+    load(0);
+    for (int c0 = 0; c0 < d; c0 += RFC) {
+        if (c0) __syncthreads();  // the last chunk has been read
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int at = (tid + 256 * q) * W;
+            *reinterpret_cast<vec_t*>(&tile[0][at / RFC][at % RFC]) = v[0][q];
+            *reinterpret_cast<vec_t*>(&tile[1][at / RFC][at % RFC]) = v[1][q];
+        }
+        __syncthreads();
+        if (c0 + RFC < d) load(c0 + RFC);
+        const int left = d - c0;
+        if (left >= RFC) {
+#pragma unroll 8
+            for (int c = 0; c < RFC; c += 4) {
+                const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&tile[0][tr][c]);
+                const f32x4_t b = *reinterpret_cast<const f32x4_t*>(&tile[1][nl][c]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc = fmaf(a[q], b[q], acc);
+            }
+        } else {
+            for (int c = 0; c < left; ++c) acc = fmaf(tile[0][tr][c], tile[1][nl][c], acc);
+        }
+    }
+    if (t0 + tr < T && n0 + nl < N) logits[(t0 + tr) * N + n0 + nl] = acc;
 }
 
 template <int NP, bool FULL, int KMAX>
@@ -749,8 +801,13 @@ hipError_t launch_router(const void* x, const void* Wr, int64_t T, int d, int N,
                                s, (const bf16_t*)x, (const bf16_t*)Wr, T, d, N, logits);
     } else {
         ProfileScope prof("router_f32", s);
-        ELB_LAUNCH(router_f32, dim3((unsigned)((T * N + 255) / 256)), dim3(256), 0, s,
-                           (const float*)x, (const float*)Wr, T, d, N, logits);
+        const dim3 grid((unsigned)((T + 15) / 16), (unsigned)((N + 15) / 16));
+        if (d % 4 == 0 && ((uintptr_t)x | (uintptr_t)Wr) % 16 == 0)
+            ELB_LAUNCH(router_f32<true>, grid, dim3(256), 0, s, (const float*)x,
+                       (const float*)Wr, T, d, N, logits);
+        else
+            ELB_LAUNCH(router_f32<false>, grid, dim3(256), 0, s, (const float*)x,
+                       (const float*)Wr, T, d, N, logits);
     }
     return hipGetLastError();
 }
