@@ -105,30 +105,33 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_vt));
 }
 
-// MODE 0 = gate_up (+SwiGLU -> H), 1 = down (-> Y); TM: rows of the block tile (64 or 128)
-template <int MODE, int TM>
+// MODE 0 = gate_up (+SwiGLU -> H), 1 = down (-> Y); TM x TN: the block tile, rows (token rows of
+// the expert) x weight rows, WM: waves along the rows; rot: first k-tile of the block, < nk; nt:
+// the weight copies carry the non-temporal hint
+template <int MODE, int TM, int TN, int WM>
 __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
                                               const int* __restrict__ row_token,
                                               const bf16_t* __restrict__ B, int e, int row0,
-                                              int rows, int ntile, int nt_count, int d, int m,
+                                              int rows, int ntile, int rot, int d, int m,
                                               bf16_t* __restrict__ C, char* sm, bool nt) {
     constexpr int TK = 64;
-    constexpr int BU = BN * TK * 2, AU = TM * TK * 2;  // bytes of a weight / token unit
-    constexpr int NB = 3, NA = (TM == 64) ? 3 : 2;     // units of each
-    constexpr int IB = BN / 32, IA = TM / 32;          // copy instructions per wave and unit
-    constexpr int FM = TM / 64;                        // 32-row token fragments per wave
-    constexpr int OUTC = (MODE == 0) ? BN / 2 : BN;    // output columns of the block
+    constexpr int BU = TN * TK * 2, AU = TM * TK * 2;  // bytes of a weight / token unit
+    constexpr int NB = 3, NA = (TM == TN) ? 2 : 3;     // units of each
+    constexpr int IB = TN / 32, IA = TM / 32;          // copy instructions per wave and unit
+    constexpr int WN = 4 / WM;
+    constexpr int FM = TM / WM / 32, FN = TN / WN / 32;  // 32-row fragments per wave
+    constexpr int OUTC = (MODE == 0) ? TN / 2 : TN;    // output columns of the block
+    constexpr int WC = OUTC / WN;                      // output columns of a wave
     constexpr int PITCH = OUTC * 2 + 16;               // bytes per row of the staged output
-    static_assert(NB * BU + NA * AU <= 5 * 128 * 128 && TM * PITCH <= 5 * 128 * 128, "LDS");
+    static_assert(NB * BU + NA * AU <= TN * 640 && TM * PITCH <= TN * 640, "LDS of the kernels");
     char* const smb = sm;
     char* const sma = sm + NB * BU;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wid >> 1, wn = wid & 1;
+    const int wm = wid / WN, wn = wid % WN;
     const int Kd = (MODE == 0) ? d : m;
     const int nk = Kd / TK;
-    const int rot = (int)((int64_t)ntile * nk / nt_count);  // first k-tile, < nk
 
     // copy sources: lane l of copy i fills physical chunk l & 7 of the unit's row
     // 8 (I wid + i) + (l >> 3) with that row's logical chunk (64-bit addresses)
@@ -147,9 +150,9 @@ __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
         const int r = 8 * (IB * wid + i) + (lane >> 3);
         int brow;
         if (MODE == 0) {
-            brow = (r < 64) ? ntile * 64 + r : m + ntile * 64 + (r - 64);
+            brow = (r < OUTC) ? ntile * OUTC + r : m + ntile * OUTC + (r - OUTC);
         } else {
-            brow = ntile * BN + r;
+            brow = ntile * TN + r;
             brow = brow < d ? brow : d - 1;  // columns past d: never stored
         }
         const int64_t src = ((int64_t)e * ((MODE == 0) ? 2 * m : d) + brow) * Kd;
@@ -191,21 +194,23 @@ __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
     };
 
     const int l32 = lane & 31, hi = lane >> 5;
-    int a_row[FM], b_row[2];
+    int a_row[FM], b_row[FN];  // gate/up: fragments 0 .. FN/2 - 1 gate, the rest matching up
 #pragma unroll
-    for (int i = 0; i < FM; ++i) a_row[i] = (wm * (TM / 2) + 32 * i + l32) * 128;
+    for (int i = 0; i < FM; ++i) a_row[i] = (wm * (TM / WM) + 32 * i + l32) * 128;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-        b_row[i] = ((MODE == 0 ? 64 * i + 32 * wn : 64 * wn + 32 * i) + l32) * 128;
+    for (int j = 0; j < FN; ++j) {
+        const int up = (MODE == 0 && j >= FN / 2) ? 1 : 0;
+        b_row[j] = (up * OUTC + WC * wn + 32 * (j - up * (FN / 2)) + l32) * 128;
+    }
     int cofs[4];  // byte offset of the chunk this lane reads for k16-step kk
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) cofs[kk] = swz8(l32, 2 * kk + hi) * 16;
 
-    f32x16_t acc[FM][2];
+    f32x16_t acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
             for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
 
@@ -240,17 +245,17 @@ __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
         const char* const pb = smb + ub * BU;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            bf16x8_t fa[FM], fb[2];
+            bf16x8_t fa[FM], fb[FN];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                fb[i] = *reinterpret_cast<const bf16x8_t*>(pb + b_row[i] + cofs[kk]);
+            for (int j = 0; j < FN; ++j)
+                fb[j] = *reinterpret_cast<const bf16x8_t*>(pb + b_row[j] + cofs[kk]);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
                 fa[i] = *reinterpret_cast<const bf16x8_t*>(pa + a_row[i] + cofs[kk]);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < FN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i],
                                                                         acc[i][j], 0, 0, 0);
         }
@@ -263,18 +268,18 @@ __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-        char* const rowp = sm + (wm * (TM / 2) + 32 * i + l32) * PITCH + hi * 8;
+        char* const rowp = sm + (wm * (TM / WM) + 32 * i + l32) * PITCH + hi * 8;
 #pragma unroll
-        for (int j = 0; j < ((MODE == 0) ? 1 : 2); ++j)
+        for (int j = 0; j < ((MODE == 0) ? FN / 2 : FN); ++j)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 float v[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float a0 = acc[i][j][4 * g + r];
-                    v[r] = (MODE == 0) ? silu(a0) * acc[i][1][4 * g + r] : a0;
+                    v[r] = (MODE == 0) ? silu(a0) * acc[i][j + FN / 2][4 * g + r] : a0;
                 }
-                const int col = ((MODE == 0) ? wn * 32 : wn * 64 + j * 32) + g * 8;
+                const int col = wn * WC + j * 32 + g * 8;
                 const u32x2_t pk = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
                 *reinterpret_cast<u32x2_t*>(rowp + col * 2) = pk;
             }
@@ -318,11 +323,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int ntile = local / tiles;
     const int row0 = offsets[e] + (local - ntile * tiles) * BM;
     const int left = offsets[e + 1] - row0;
+    const int rot = (int)((int64_t)ntile * (((MODE == 0) ? d : m) / 64) / nt_count);
     if (left <= 64)
-        gemm_mid_body<MODE, 64>(A, row_token, B, e, row0, left, ntile, nt_count, d, m, C, sm, tiles == 1);
+        gemm_mid_body<MODE, 64, BN, 2>(A, row_token, B, e, row0, left, ntile, rot, d, m, C, sm,
+                                       tiles == 1);
     else
-        gemm_mid_body<MODE, 128>(A, row_token, B, e, row0, left < BM ? left : BM, ntile,
-                                 nt_count, d, m, C, sm, tiles == 1);
+        gemm_mid_body<MODE, 128, BN, 2>(A, row_token, B, e, row0, left < BM ? left : BM, ntile,
+                                        rot, d, m, C, sm, tiles == 1);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -440,11 +447,30 @@ __device__ __forceinline__ void gemm_dma_body(
     int e, row0, rows;
     find_tile(tile_off, offsets, N, tile, TM, e, row0, rows);
 
+    const int Kd = (MODE == 0) ? d : m;
+    const bool alone = tile_off[e + 1] - tile_off[e] == 1;
+    const int rot = alone && (ntile & 1) ? Kd / TK / 2 : 0;  // see the pipeline below
+    // An expert's last tile with at most 128 rows: the smaller tile forms of the mid-sized kernel,
+    // as wide as this one's, 3 x (16 + 32) KB of LDS at most (64 rows: per k-tile 40 KB copied and
+    // 64 KB read instead of 64 and 128, and a quarter of the MFMAs).  OLMoE-shaped layer, us:
+    // 2300 tokens 380 -> 360, 8192 tokens top-8 950 -> 907, 16384 tokens 1603 -> 1572; the sizes
+    // without such tiles as before.  Taken in order: all of them after the full tiles would
+    // balance the units better, but reads their experts' weights from HBM again (3000 tokens 391
+    // -> 439, 4096 top-8 496 -> 490).
+    if (rows <= 128) {
+        if (rows <= 64)
+            gemm_mid_body<MODE, 64, TN, 1>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
+                                           sm_bytes, NTW);
+        else
+            gemm_mid_body<MODE, 128, TN, 2>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
+                                            sm_bytes, NTW);
+        return;
+    }
+
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wid = tid >> 6;
     const int wm = wid >> 1, wn = wid & 1;
-    const int Kd = (MODE == 0) ? d : m;
 
     // Copy sources: wave w copies rows [64w, 64w + 64) of each tile, 8 rows (1 KB) per
     // instruction; lane l fills physical chunk l & 7 of row 64w + 8i + (l >> 3), so it
@@ -574,8 +600,6 @@ __device__ __forceinline__ void gemm_dma_body(
     // the rows of every point in use have to fit there.  With more M-tiles, where the weights are
     // shared too, all blocks stay in step (4096 tokens with 8 points: 447 -> 466 us).
     const int nk = Kd / TK;  // >= 1
-    const bool alone = tile_off[e + 1] - tile_off[e] == 1;
-    const int rot = alone && (ntile & 1) ? nk / 2 : 0;
     auto k_of = [&](int t) { return (t + rot < nk ? t + rot : t + rot - nk) * TK; };
     // as if barriers at t = -3, -2, -1 had issued B(0); A(0), B(1); A(1), B(2)
     issue(Bblk, b_off, 0, k_of(0), NTW);

@@ -32,3 +32,24 @@ def test_mid_tile_edges(d, m):
     ref = O.moe_experts(L.x, L.W_gu, L.W_down, k, ids, w.astype(np.float64))
     # bf16 storage of H and of the expert output: two roundings of 2^-9 relative
     assert rel_err_rows(cpu(y), ref).max() < RTOL_BF16
+
+
+@pytest.mark.parametrize("d", [192, 512])
+def test_large_kernel_short_tiles(d):
+    """The 256-row kernel's tiles of at most 64 and 128 rows: alone (experts of 1, 40, 65 and 128
+    rows) and behind full tiles (256 + 33 .. 129 rows), a last N-tile of 192 of 256 columns
+    (d = 192), an odd number of k-tiles with a rotated start (d = 192: three)."""
+    counts = [1, 40, 65, 128, 289, 320, 321, 384, 385, 700, 900]
+    N, T, m = len(counts), sum(counts), 1024
+    assert T // N >= 112 and (T + 128 * N) // 256 * (m // 128) > 128  # the 256-row kernel
+    L = synth.moe_layer(T, d, N, m, dtype="bf16", seed=d)
+    rng = np.random.default_rng(d)
+    ids = rng.permutation(np.repeat(np.arange(N), counts)).astype(np.int32)[:, None]
+    k = np.ones(T, np.int32)
+    w = rng.uniform(0.1, 1.0, (T, 1)).astype(np.float32)
+    x, Wgu, Wd = (to_gpu(a, torch.bfloat16) for a in (L.x, L.W_gu, L.W_down))
+    y = B.elb_moe_experts(x, Wgu, Wd, to_gpu(k, torch.int32), to_gpu(ids, torch.int32),
+                          to_gpu(w))
+    torch.cuda.synchronize()
+    ref = O.moe_experts(L.x, L.W_gu, L.W_down, k, ids, w.astype(np.float64))
+    assert rel_err_rows(cpu(y), ref).max() < RTOL_BF16
