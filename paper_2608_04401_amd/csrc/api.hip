@@ -288,7 +288,7 @@ int elb_router_route(const void* x, const void* W_router, int64_t T, int32_t d, 
     if (!x || !W_router || !k || !ids || !w)
         return fail(ELB_ERR_INVALID_ARG, "NULL tensor pointer");
     if (router_route_dma_usable(dtype, T, d, N, params->K))
-        return hip_status(launch_router_route_dma(x, W_router, T, d, *params, logits_out, k,
+        return hip_status(launch_router_route_dma(x, W_router, T, d, N, *params, logits_out, k,
                                                   ids, w, nullptr, 0, (hipStream_t)stream),
                           "router_route");
     return hip_status(launch_router_route(x, W_router, T, d, N, *params, logits_out, k, ids, w,
@@ -481,16 +481,15 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
     int* k = k_out ? k_out : (int*)(ws + L.k);
     int* ids = ids_out ? ids_out : (int*)(ws + L.ids);
     float* w = w_out ? w_out : (float*)(ws + L.w);
-    // Router and routing, by size (the same bits on every path): large batches with N = 64
-    // and d % 256 == 0 split the contraction over four blocks per 64 tokens (two launches; the
-    // second also writes the dispatch histogram); small batches with N = 64 take one wave per
-    // (16 tokens, 16 experts, quarter of the contraction), then the same 16-lane split
-    // routing; the rest the fused one-block kernel, or the router and routing kernels for
-    // fp32 and caps above 16.
+    // Router and routing, by size (the same bits on every path): up to kRouteDmaMaxT tokens one
+    // launch of 16-token blocks, which also writes the dispatch histogram; larger batches with
+    // N = 64 and d % 256 == 0 split the contraction over four blocks per 64 tokens (two
+    // launches, histogram included); the rest the fused one-block kernel, or the router and
+    // routing kernels for fp32 and caps above 16.
     const bool skinny = gemm_use_skinny(dtype, T, K, N, d, m);
     if (router_route_dma_usable(dtype, T, d, N, K)) {
         if (int rc = hip_status(
-                launch_router_route_dma(x, W_router, T, d, *params, logits_out, k, ids, w,
+                launch_router_route_dma(x, W_router, T, d, N, *params, logits_out, k, ids, w,
                                         (int*)(ws + L.hist), dispatch_hist_ld(T), s),
                 "router_route_dma"))
             return rc;
@@ -507,17 +506,7 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
         return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                             dtype, y, ws, L, counts_out, s, true, split_hist_subs(T));
     }
-    if (router_slices_usable(dtype, T, N, K)) {
-        if (int rc = hip_status(
-                launch_router_slices_route(x, W_router, T, d, *params, (float*)(ws + L.part),
-                                           logits_out, k, ids, w, (int*)(ws + L.hist),
-                                           dispatch_hist_ld(T), s),
-                "router_slices_route"))
-            return rc;
-        return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
-                            dtype, y, ws, L, counts_out, s, true, split_hist_subs(T));
-    }
-    if (router_route_fusable(dtype, K) && !(N == 64 && T <= kSmallBatch)) {
+    if (router_route_fusable(dtype, K)) {
         if (int rc = hip_status(launch_router_route(x, W_router, T, d, N, *params, logits_out,
                                                     k, ids, w, s), "router_route"))
             return rc;

@@ -108,7 +108,7 @@ hipError_t launch_router_route(const void* x, const void* Wr, int64_t T, int d, 
 // into part [4, T, 64] (workspace), then their sum and the routing; also writes the dispatch
 // histogram: split_hist_subs(T) histograms [64, hist_ld] (column g = tokens [64 g, 64 g + 64),
 // or its quarter j in histogram j).  Same bits as the other router paths.
-// router + routing in one launch (N = 64, d % 256 == 0, at most kRouteDmaMaxT tokens,
+// router + routing in one launch (bf16, d % 32 == 0, at most kRouteDmaMaxT tokens,
 // K <= kLaneMaxK): 16 tokens per block, the contraction's quarters in the block's four waves;
 // the same bits as the split form; hist (optional) as launch_router_split_route writes it
 // (kHistSubs histograms, group-major)
@@ -116,7 +116,7 @@ constexpr int64_t kRouteDmaMaxT = 4096;
 static_assert(kRouteDmaMaxT <= 64 * kDirectGroups, "the one-launch form writes kHistSubs "
                                                    "histograms");
 bool router_route_dma_usable(int dtype, int64_t T, int d, int N, int K);
-hipError_t launch_router_route_dma(const void* x, const void* Wr, int64_t T, int d,
+hipError_t launch_router_route_dma(const void* x, const void* Wr, int64_t T, int d, int N,
                                    const elb_route_params& p, float* logits, int* k, int* ids,
                                    float* w, int* hist, int64_t hist_ld, hipStream_t s);
 bool router_split_usable(int dtype, int64_t T, int d, int N, int K);
@@ -124,16 +124,6 @@ hipError_t launch_router_split_route(const void* x, const void* Wr, int64_t T, i
                                      const elb_route_params& p, float* part, float* logits,
                                      int* k, int* ids, float* w, int* hist, int64_t hist_ld,
                                      hipStream_t s);
-
-// the layer's router and routing for batches of at most kSmallBatch tokens with N == 64
-// (bf16, K <= kLaneMaxK): one wave per (16 tokens, 16 experts, quarter of the contraction)
-// into part [4, T, 64], then the 16-lane split routing (histograms as above, split_hist_subs(T)
-// of them).  Same bits as the other router paths.
-bool router_slices_usable(int dtype, int64_t T, int N, int K);
-hipError_t launch_router_slices_route(const void* x, const void* Wr, int64_t T, int d,
-                                      const elb_route_params& p, float* part, float* logits,
-                                      int* k, int* ids, float* w, int* hist, int64_t hist_ld,
-                                      hipStream_t s);
 
 // grouped GEMMs
 // rows per M-tile of the grouped GEMMs for this problem (the dispatch scan uses the same)

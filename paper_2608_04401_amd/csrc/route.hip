@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void route_x16_kernel(const float* __restrict_
     }
     __syncthreads();
     const int tr = threadIdx.x >> 4;
-    route_token_x16<KMAX>(&rows[tr][0], K, eps, mode, renorm, xt, t0 + tr, t0 + tr < T, kout,
+    route_token_x16<KMAX>(&rows[tr][0], 64, K, eps, mode, renorm, xt, t0 + tr, t0 + tr < T, kout,
                           ids, wout);
 }
 

@@ -382,7 +382,7 @@ __device__ __forceinline__ void route_token(const float* row, int N, int K, floa
         });
 }
 
-// ---- one token by 16 lanes (N = 64): for latency, where few tokens are routed at once ----
+// ---- one token by 16 lanes: for latency, where few tokens are routed at once ----
 //
 // The same keys, u, S, deviations, first argmin and weights as route_token, bit for bit, with
 // the work spread over 16 consecutive lanes of a wave, one 16-lane DPP row (lane sl holds
@@ -438,13 +438,13 @@ __device__ __forceinline__ float row_last(float v) {
     return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x10 | (0x0f << 5)));
 }
 
-// row: the token's 64 logits in LDS; every lane of the group calls this (valid: the token
-// exists; only valid groups write)
+// row: the token's 64 logits in LDS, -inf past the N experts; every lane of the group calls this
+// (valid: the token exists; only valid groups write)
 // lds_hist (optional): a 64-bin LDS histogram to which each selected expert of a valid token
 // adds one (the dispatch's per-group counts).
 template <int KMAX>
-__device__ __forceinline__ void route_token_x16(float* row, int K, float eps, int mode,
-                                                int renorm, const XTable& xt, int64_t t,
+__device__ __forceinline__ void route_token_x16(float* row, int N, int K, float eps,
+                                                int mode, int renorm, const XTable& xt, int64_t t,
                                                 bool valid, int* __restrict__ kout,
                                                 int* __restrict__ ids,
                                                 float* __restrict__ wout,
@@ -501,13 +501,20 @@ __device__ __forceinline__ void route_token_x16(float* row, int K, float eps, in
     float u[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) u[i] = rel_exp(key[i], nl);
-    // ---- S over the ranks (tree_sum by a butterfly), u_min = u of rank 63 ----
+    // ---- S over the ranks (tree_sum by a butterfly), u_min = u of rank N - 1 ----
     float S = (u[0] + u[1]) + (u[2] + u[3]);
     S += xor16f<1>(S);
     S += xor16f<2>(S);
     S += xor16f<4>(S);
     S += xor16f<8>(S);
-    const float umin = row_last(u[3]);
+    float umin;
+    if (N == NP) {  // uniform
+        umin = row_last(u[3]);
+    } else {
+        const int at = N - 1;
+        const float uq = (at & 2) ? ((at & 1) ? u[3] : u[2]) : ((at & 1) ? u[1] : u[0]);
+        umin = __shfl(uq, (threadIdx.x & 48) | (at >> 2));
+    }
     int k = K;
     if (mode == ELB_MODE_ELBOW) {
         const float Rp = (1.0f - umin) + eps * S;

@@ -30,13 +30,12 @@ __device__ __forceinline__ void router_slice(int d, int s, int& first, int& coun
 // each wave's partial sums over its k-steps go to part[w] (lane rows, expert columns
 // 16 g + ..., g < NG); the caller sums the RW partial tiles.  Every logit is computed the same
 // way whatever NG and g0 are (its own MFMA column, the same k-steps per wave, the same sum).
-// w: the slice (by default the wave's index in the block).
 template <int NG>
 __device__ __forceinline__ void router_partials(const bf16_t* __restrict__ x,
                                                 const bf16_t* __restrict__ Wr, int64_t T,
                                                 int d, int N, int64_t t0, int g0,
-                                                float (&part)[RW][16][65],
-                                                int w = threadIdx.x >> 6) {
+                                                float (&part)[RW][16][65]) {
+    const int w = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int l16 = lane & 15;
     const int kq = (lane >> 4) * 8;
@@ -129,31 +128,6 @@ __global__ __launch_bounds__(64 * RW) void router_bf16(const bf16_t* __restrict_
     }
 }
 
-// Batches of at most kSmallBatch tokens with N = 64 (decode): one wave per (16 tokens, 16
-// experts, slice s of the contraction), so that the x and W_r reads spread over four times as
-// many compute units as in router_bf16<1> (32 KB per block instead of 128 KB); the partial
-// tile goes to part [4, T, 64], and route_split_sum_x16 sums the four slices in order and
-// routes them (the same bits as router_bf16's LDS sum and every other router path).
-__global__ __launch_bounds__(64) void router_slice_bf16(const bf16_t* __restrict__ x,
-                                                        const bf16_t* __restrict__ Wr,
-                                                        int64_t T, int d,
-                                                        float* __restrict__ part) {
-    __shared__ float tile[RW][16][65];  // only row blockIdx.z is used
-    const int64_t t0 = (int64_t)blockIdx.x * 16;
-    const int g0 = (int)blockIdx.y, s = (int)blockIdx.z;
-    router_partials<1>(x, Wr, T, d, 64, t0, g0, tile, s);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int o = threadIdx.x + 64 * q;
-        const int tr = o >> 4, nl = o & 15;
-        const int64_t t = t0 + tr;
-        if (t < T) part[((int64_t)s * T + t) * 64 + 16 * g0 + nl] = tile[s][tr][nl];
-    }
-}
-
 // Router GEMM and routing fused: the block's 16 x N logits are summed into LDS and routed
 // there, so the logits need not travel through HBM; they are written out only when `logits`
 // is not null.  N = 64: 16 lanes per token (route_token_x16); otherwise one lane per token
@@ -181,7 +155,7 @@ __global__ __launch_bounds__(64 * RW) void router_route_bf16(
     if constexpr (NP == 64 && FULL) {
         // 16 lanes per token: wave w routes the block's tokens 4 w .. 4 w + 3
         const int tr = threadIdx.x >> 4;
-        route_token_x16<KMAX>(&part[0][tr][0], K, eps, mode, renorm, xt, t0 + tr,
+        route_token_x16<KMAX>(&part[0][tr][0], 64, K, eps, mode, renorm, xt, t0 + tr,
                               t0 + tr < T, kout, ids, wout);
     } else {
         if (threadIdx.x < 16 && t0 + threadIdx.x < T)
@@ -433,7 +407,7 @@ __global__ __launch_bounds__(256) void route_split_sum_x16(const float* __restri
     row[4 * sl + 2] = l2;
     row[4 * sl + 3] = l3;
     __syncthreads();  // h zeroed (and the rows written) before any count
-    route_token_x16<KMAX>(row, K, eps, mode, renorm, xt, t, valid, kout, ids, wout, h);
+    route_token_x16<KMAX>(row, 64, K, eps, mode, renorm, xt, t, valid, kout, ids, wout, h);
     __syncthreads();
     if (threadIdx.x < 64) {
         const int64_t j = blockIdx.x % kHistSubs, g = blockIdx.x / kHistSubs;
@@ -450,103 +424,110 @@ __global__ __launch_bounds__(256) void route_split_sum_x16(const float* __restri
 // quarter a wave copies the 64 W_r rows and the block's 16 x rows (one 128-byte line per row,
 // 16-byte chunks XOR-swizzled by row) straight into its own LDS ring with
 // global_load_lds_dwordx4, kDmaRing - 1 chunks ahead, and waits only for its own copies: the
-// loop has no barrier.  The MFMA chains, the sum ((P0 + P1) + P2) + P3 and the 16-lane routing
+// loop has no barrier.  A quarter of an odd number of 32-deep steps (d % 256 != 0) ends in half
+// a chunk.  Experts are taken in groups of 16 (NG of them; rows past N repeat row N - 1), and
+// logits past N are -inf: they sort last, add exact zeros to S and never win the argmin, so
+// every N gives the bits of the one-lane routing.  The MFMA chains, the sum ((P0 + P1) + P2) + P3 and the 16-lane routing
 // (route_token_x16) are those of router_split_bf16 + route_split_sum_x16, so the logits,
 // k, ids and weights are the same bits.  hist (optional): the block's per-expert assignment
 // counts go to histogram b % 4, row b / 4, as route_split_sum_x16 writes them (the grid has
 // four blocks per 64-token group; blocks past the last token write zero counts).
 constexpr int kDmaRing = 4;                // chunks in a wave's ring
-constexpr int kDmaSlot = (64 + 16) * 128;  // bytes per chunk: 64 W_r rows, then 16 x rows
-constexpr int kDmaWave = kDmaRing * kDmaSlot;
 
-template <int KMAX>
+// FULL: N == 64 and d % 256 == 0 (no expert past N, no half chunk), without those tests
+template <int KMAX, int NG, bool FULL>
 __global__ __launch_bounds__(256) void router_route_dma(
-    const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wr, int64_t T, int d, int K,
-    float eps, int mode, int renorm, XTable xt, float* __restrict__ logits,
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wr, int64_t T, int d, int n_experts,
+    int K, float eps, int mode, int renorm, XTable xt, float* __restrict__ logits,
     int* __restrict__ kout, int* __restrict__ ids, float* __restrict__ wout,
     int* __restrict__ hist, int64_t hist_ld) {
+    const int N = FULL ? 64 : n_experts;
+    constexpr int kDmaSlot = (NG + 1) * 16 * 128;  // bytes per chunk: W_r rows, then 16 x rows
+    constexpr int kDmaWave = kDmaRing * kDmaSlot;
     // the four rings take all of LDS; after the loop a wave's partial tile [16][65] lies at the
     // start of its own ring, and the 64-bin histogram in wave 1's
     __shared__ __attribute__((aligned(1024))) char sm[RW * kDmaWave];
     const int64_t t0 = (int64_t)blockIdx.x * 16;
     if (t0 >= T) {  // a quarter past the last token of the last group: zero counts only
-        if (hist && threadIdx.x < 64)
-            hist[((int64_t)(blockIdx.x % kHistSubs) * hist_ld + blockIdx.x / kHistSubs) * 64 +
+        if (hist && threadIdx.x < N)
+            hist[((int64_t)(blockIdx.x % kHistSubs) * hist_ld + blockIdx.x / kHistSubs) * N +
                  threadIdx.x] = 0;
         return;  // block-uniform, before any barrier
     }
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
     int first, steps;
-    router_slice(d, w, first, steps);  // d % 256 == 0: first and steps are even
-    const int c0 = first / 2, nc = steps / 2;
+    router_slice(d, w, first, steps);
+    const int nc = (steps + 1) / 2;
     const bf16_t* const xb = x + t0 * d;  // the block's first token row
-    // copy sources: W_r rows 8 i + (lane >> 3) (i < 8) and x rows 8 i + (lane >> 3) (i < 2);
+    // copy sources: W_r rows 8 i + (lane >> 3) (i < 2 NG) and x rows 8 i + (lane >> 3) (i < 2);
     // lane l fills physical chunk l & 7 of its row, i.e. it fetches logical chunk
-    // (l & 7) ^ (row & 7).  Rows past T repeat the last token's row (never stored).
-    uint32_t woff[8], xoff[2];
+    // (l & 7) ^ (row & 7) (of half a chunk: one of its four, the upper half is never read).
+    // Rows past N and past T repeat the last row (never stored).
+    const uint32_t q16 = (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u;
+    uint32_t woff[2 * NG], xoff[2];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 2 * NG; ++i) {
         const int r = 8 * i + (lane >> 3);
-        const int q = (lane & 7) ^ (r & 7);
-        woff[i] = ((uint32_t)r * (uint32_t)d + c0 * 64 + q * 8) * 2u;
+        woff[i] = ((uint32_t)(r < N ? r : N - 1) * (uint32_t)d + first * 32) * 2u;
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int r = 8 * i + (lane >> 3);
-        const int q = (lane & 7) ^ (r & 7);
         const int tr = (t0 + r < T) ? r : (int)(T - 1 - t0);
-        xoff[i] = ((uint32_t)tr * (uint32_t)d + c0 * 64 + q * 8) * 2u;
+        xoff[i] = ((uint32_t)tr * (uint32_t)d + first * 32) * 2u;
     }
     char* const ring = sm + w * kDmaWave;
     const uint32_t lds_ring =
         __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)ring);
     auto issue = [&](int c, int slot) {  // chunk c of the quarter into ring slot `slot`
         const uint32_t base = lds_ring + slot * kDmaSlot;
+        const uint32_t o = c * 128 + (FULL || 2 * c + 1 < steps ? q16 : q16 & 63u);
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 2 * NG; ++i)
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(base + i * 1024), "v"(woff[i] + c * 128), "s"(Wr)
+                         :: "s"(base + i * 1024), "v"(woff[i] + o), "s"(Wr)
                          : "memory", "m0");
 #pragma unroll
         for (int i = 0; i < 2; ++i)
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(base + 64 * 128 + i * 1024), "v"(xoff[i] + c * 128), "s"(xb)
+                         :: "s"(base + NG * 2048 + i * 1024), "v"(xoff[i] + o), "s"(xb)
                          : "memory", "m0");
     };
-    f32x4_t acc[4];
+    f32x4_t acc[NG];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < NG; ++g) acc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int l16 = lane & 15, hq = lane >> 4;
 #pragma unroll
     for (int p = 0; p < kDmaRing - 1; ++p)
         if (p < nc) issue(p, p);
     for (int c = 0; c < nc; ++c) {
         // chunk c is in when at most the copies of the chunks issued after it (at most
-        // kDmaRing - 2 of them, ten instructions each) are in flight; its slot's previous
+        // kDmaRing - 2 of them, 2 NG + 2 instructions each) are in flight; its slot's previous
         // chunk (c - 1) was read before its MFMAs, so it is free for chunk c + kDmaRing - 1
         const int left = nc - 1 - c;
         static_assert(kDmaRing == 4, "wait counts below");
-        if (left >= 2) ELB_WAIT_VMCNT(20);
-        else if (left == 1) ELB_WAIT_VMCNT(10);
+        if (left >= 2) ELB_WAIT_VMCNT(2 * (2 * NG + 2));
+        else if (left == 1) ELB_WAIT_VMCNT(2 * NG + 2);
         else ELB_WAIT_VMCNT(0);
         // the copies write LDS behind the compiler's back: keep this chunk's reads below the wait
         asm volatile("" ::: "memory");
         if (c + kDmaRing - 1 < nc) issue(c + kDmaRing - 1, (c + kDmaRing - 1) % kDmaRing);
         const char* const sl = ring + (c % kDmaRing) * kDmaSlot;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {  // the chunk's two 32-deep k-steps
+        for (int j = 0; j < 2; ++j) {  // the chunk's two 32-deep k-steps (half a chunk: one)
+            if (!FULL && 2 * c + j >= steps) break;
             const int q = 4 * j + hq;  // logical 16-byte chunk of this lane's 8 k values
             const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(
-                sl + 64 * 128 + l16 * 128 + ((q ^ (l16 & 7)) << 4));
-            bf16x8_t b[4];
+                sl + NG * 2048 + l16 * 128 + ((q ^ (l16 & 7)) << 4));
+            bf16x8_t b[NG];
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < NG; ++g) {
                 const int n = 16 * g + l16;
                 b[g] = *reinterpret_cast<const bf16x8_t*>(sl + n * 128 + ((q ^ (n & 7)) << 4));
             }
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int g = 0; g < NG; ++g)
                 acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[g], acc[g], 0, 0, 0);
         }
     }
@@ -554,7 +535,7 @@ __global__ __launch_bounds__(256) void router_route_dma(
     // own ring: every copy into the ring has landed and every read of it has been used
     float* const pw = reinterpret_cast<float*>(ring);
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
         for (int r = 0; r < 4; ++r) pw[(4 * hq + r) * 65 + 16 * g + l16] = acc[g][r];
     __syncthreads();  // every wave is past its loop and its partial tile is written
@@ -570,26 +551,30 @@ __global__ __launch_bounds__(256) void router_route_dma(
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int n = 4 * sl + i;
-        const float* p0 = reinterpret_cast<const float*>(sm) + tr * 65 + n;
-        float v = p0[0];
+        l4[i] = -INFINITY;
+        if (n < N) {
+            const float* p0 = reinterpret_cast<const float*>(sm) + tr * 65 + n;
+            float v = p0[0];
 #pragma unroll
-        for (int ww = 1; ww < RW; ++ww) v += p0[ww * (kDmaWave / 4)];
-        l4[i] = v;
+            for (int ww = 1; ww < RW; ++ww) v += p0[ww * (kDmaWave / 4)];
+            l4[i] = v;
+        }
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) row[4 * sl + i] = l4[i];
     if (logits && valid) {
-        float* const lt = logits + t * 64 + 4 * sl;
+        float* const lt = logits + t * N + 4 * sl;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lt[i] = l4[i];
+        for (int i = 0; i < 4; ++i)
+            if (4 * sl + i < N) lt[i] = l4[i];
     }
     __syncthreads();  // the logit rows and the zeroed histogram before any count
-    route_token_x16<KMAX>(row, K, eps, mode, renorm, xt, t, valid, kout, ids, wout, h);
+    route_token_x16<KMAX>(row, N, K, eps, mode, renorm, xt, t, valid, kout, ids, wout, h);
     if (!hist) return;  // kernel-uniform
     __syncthreads();
-    if (threadIdx.x < 64) {
+    if (threadIdx.x < N) {
         const int64_t j = blockIdx.x % kHistSubs, g = blockIdx.x / kHistSubs;
-        hist[(j * hist_ld + g) * 64 + threadIdx.x] = h[threadIdx.x];
+        hist[(j * hist_ld + g) * N + threadIdx.x] = h[threadIdx.x];
     }
 }
 
@@ -702,25 +687,41 @@ hipError_t launch_router_route(const void* x, const void* Wr, int64_t T, int d, 
 bool router_route_dma_usable(int dtype, int64_t T, int d, int N, int K) {
     // up to one 16-token block per compute unit (256 on MI355X): above that a second round
     // of blocks costs more than the split form's second launch (measured at 6144 tokens)
-    return dtype == ELB_BF16 && N == 64 && K <= kLaneMaxK && T > 0 && T <= kRouteDmaMaxT &&
-           d % 256 == 0 && d <= (1 << 20);
+    return dtype == ELB_BF16 && N >= 2 && N <= 64 && K <= kLaneMaxK && T > 0 &&
+           T <= kRouteDmaMaxT && d % 32 == 0 && d <= (1 << 20);
 }
 
-hipError_t launch_router_route_dma(const void* x, const void* Wr, int64_t T, int d,
+template <int NG, bool FULL>
+static void launch_rrd(const void* x, const void* Wr, int64_t T, int d, int N,
+                       const elb_route_params& p, float* logits, int* k, int* ids, float* w,
+                       int* hist, int64_t hist_ld, hipStream_t s) {
+    const dim3 grid((unsigned)(dispatch_groups(T) * kHistSubs));  // every histogram quarter
+    const XTable xt = make_xtable(N);
+    if (p.K <= 8)
+        ELB_LAUNCH((router_route_dma<8, NG, FULL>), grid, dim3(256), 0, s, (const bf16_t*)x,
+                   (const bf16_t*)Wr, T, d, N, p.K, p.eps, p.mode, p.renormalize, xt, logits, k,
+                   ids, w, hist, hist_ld);
+    else
+        ELB_LAUNCH((router_route_dma<kLaneMaxK, NG, FULL>), grid, dim3(256), 0, s, (const bf16_t*)x,
+                   (const bf16_t*)Wr, T, d, N, p.K, p.eps, p.mode, p.renormalize, xt, logits, k,
+                   ids, w, hist, hist_ld);
+}
+
+hipError_t launch_router_route_dma(const void* x, const void* Wr, int64_t T, int d, int N,
                                    const elb_route_params& p, float* logits, int* k, int* ids,
                                    float* w, int* hist, int64_t hist_ld, hipStream_t s) {
     if (T == 0) return hipSuccess;
     ProfileScope prof("router_route_dma", s);
-    const dim3 grid((unsigned)(dispatch_groups(T) * kHistSubs));  // every histogram quarter
-    const XTable xt = make_xtable(64);
-    if (p.K <= 8)
-        ELB_LAUNCH(router_route_dma<8>, grid, dim3(256), 0, s, (const bf16_t*)x,
-                   (const bf16_t*)Wr, T, d, p.K, p.eps, p.mode, p.renormalize, xt, logits, k,
-                   ids, w, hist, hist_ld);
+    if (N == 64 && d % 256 == 0)
+        launch_rrd<4, true>(x, Wr, T, d, N, p, logits, k, ids, w, hist, hist_ld, s);
+    else if (N > 48)
+        launch_rrd<4, false>(x, Wr, T, d, N, p, logits, k, ids, w, hist, hist_ld, s);
+    else if (N > 32)
+        launch_rrd<3, false>(x, Wr, T, d, N, p, logits, k, ids, w, hist, hist_ld, s);
+    else if (N > 16)
+        launch_rrd<2, false>(x, Wr, T, d, N, p, logits, k, ids, w, hist, hist_ld, s);
     else
-        ELB_LAUNCH(router_route_dma<kLaneMaxK>, grid, dim3(256), 0, s, (const bf16_t*)x,
-                   (const bf16_t*)Wr, T, d, p.K, p.eps, p.mode, p.renormalize, xt, logits, k,
-                   ids, w, hist, hist_ld);
+        launch_rrd<1, false>(x, Wr, T, d, N, p, logits, k, ids, w, hist, hist_ld, s);
     return hipGetLastError();
 }
 
@@ -758,32 +759,6 @@ hipError_t launch_router_split_route(const void* x, const void* Wr, int64_t T, i
     else
         ELB_LAUNCH(route_split_sum<kLaneMaxK>, dim3(groups), dim3(64), 0, s, part, T, p.K,
                    p.eps, p.mode, p.renormalize, xt, logits, k, ids, w, hist, hist_ld);
-    return hipGetLastError();
-}
-
-bool router_slices_usable(int dtype, int64_t T, int N, int K) {
-    return dtype == ELB_BF16 && N == 64 && K <= kLaneMaxK && T > 0 && T <= kSmallBatch;
-}
-
-hipError_t launch_router_slices_route(const void* x, const void* Wr, int64_t T, int d,
-                                      const elb_route_params& p, float* part, float* logits,
-                                      int* k, int* ids, float* w, int* hist, int64_t hist_ld,
-                                      hipStream_t s) {
-    if (T == 0) return hipSuccess;
-    {
-        ProfileScope prof("router_slice_bf16", s);
-        ELB_LAUNCH(router_slice_bf16, dim3((unsigned)((T + 15) / 16), 4, RW), dim3(64), 0, s,
-                   (const bf16_t*)x, (const bf16_t*)Wr, T, d, part);
-    }
-    ProfileScope prof("route_split_sum", s);
-    const dim3 grid((unsigned)(dispatch_groups(T) * kHistSubs));
-    const XTable xt = make_xtable(64);
-    if (p.K <= 8)
-        ELB_LAUNCH(route_split_sum_x16<8>, grid, dim3(256), 0, s, part, T, p.K, p.eps, p.mode,
-                   p.renormalize, xt, logits, k, ids, w, hist, hist_ld);
-    else
-        ELB_LAUNCH(route_split_sum_x16<kLaneMaxK>, grid, dim3(256), 0, s, part, T, p.K, p.eps,
-                   p.mode, p.renormalize, xt, logits, k, ids, w, hist, hist_ld);
     return hipGetLastError();
 }
 

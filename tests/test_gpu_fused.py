@@ -111,11 +111,10 @@ def test_layer_split_router_equals_fused(T, d, K, mode):
                                         (100, 320, 8, B.MODE_ELBOW), (777, 192, 12, B.MODE_TOPK),
                                         (1, 256, 8, B.MODE_ELBOW), (65, 1024, 8, B.MODE_TOPK)])
 def test_layer_small_batch_router_equals_fused(T, d, K, mode):
-    """Batches of at most 1024 tokens with N = 64: with d % 256 == 0 the layer takes the
-    one-launch router + routing, otherwise one wave per (16 tokens, 16 experts, quarter of the
-    contraction) and the quarters summed in the 16-lane split routing.  Its logits, k, ids and
-    w must be the fused entry point's bits and the two-step path's, its per-expert counts those
-    of its routing, and its output the expert stage's bits on the same routing."""
+    """Batches of at most 1024 tokens with N = 64, d % 256 == 0 and not: the one-launch router +
+    routing.  The layer's logits, k, ids and w must be the fused entry point's bits and the
+    two-step path's, its per-expert counts those of its routing, and its output the expert
+    stage's bits on the same routing."""
     L = synth.moe_layer(T, d, 64, 128, dtype="bf16", seed=T + d + 1)
     x, Wr, Wgu, Wd = (to_gpu(a, BF) for a in (L.x, L.W_router, L.W_gu, L.W_down))
     y, dbg = B.elb_moe_forward(x, Wr, Wgu, Wd, K=K, mode=mode, debug=True)
@@ -131,3 +130,46 @@ def test_layer_small_batch_router_equals_fused(T, d, K, mode):
     y2 = B.elb_moe_experts(x, Wgu, Wd, k, ids, w)
     torch.cuda.synchronize()
     assert torch.equal(y, y2)
+
+
+@pytest.mark.parametrize("T,d,N,K", [(1, 64, 2, 1), (70, 64, 5, 5), (257, 192, 8, 8),
+                                     (1000, 320, 15, 4), (130, 448, 16, 16), (4096, 128, 17, 8),
+                                     (300, 576, 31, 9), (513, 832, 32, 8), (64, 1088, 33, 16),
+                                     (2000, 896, 48, 8), (100, 704, 49, 2), (999, 256, 60, 8),
+                                     (333, 2496, 63, 16)])
+@pytest.mark.parametrize("mode,eps,renorm", [(B.MODE_ELBOW, 0.0, True), (B.MODE_TOPK, 1e-8, False)])
+def test_layer_one_launch_router_any_shape(T, d, N, K, mode, eps, renorm):
+    """The one-launch router + routing with fewer than 64 experts (every number of 16-expert
+    groups, at its edges) and quarters of odd and unequal numbers of 32-deep steps: the bits of
+    the router kernel followed by the one-lane routing kernels, and the dispatch histogram (the
+    layer's output is the bits of the expert stage, which counts the assignments itself)."""
+    L = synth.moe_layer(T, d, N, 64, dtype="bf16", seed=T + d + N)
+    x, Wr, Wgu, Wd = (to_gpu(a, BF) for a in (L.x, L.W_router, L.W_gu, L.W_down))
+    y, dbg = B.elb_moe_forward(x, Wr, Wgu, Wd, K=K, eps=eps, mode=mode, renormalize=renorm,
+                               debug=True)
+    lg = B.elb_router_logits(x, Wr)
+    k, ids, w = B.elb_route(lg, K=K, eps=eps, mode=mode, renormalize=renorm)
+    torch.cuda.synchronize()
+    assert torch.equal(dbg["logits"], lg)
+    assert torch.equal(dbg["k"], k) and torch.equal(dbg["ids"], ids) and torch.equal(dbg["w"], w)
+    ii = cpu(ids)
+    assert np.array_equal(cpu(dbg["counts"]), np.bincount(ii[ii >= 0], minlength=N))
+    y2 = B.elb_moe_experts(x, Wgu, Wd, k, ids, w)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+
+
+@pytest.mark.parametrize("N,K", [(5, 3), (24, 8), (60, 8)])
+def test_one_launch_router_ties(N, K):
+    """Equal logits (identical W_r rows in pairs, and a zero token whose logits are all equal):
+    ties go to the lower id and a flat curve to k = 1, as in the one-lane kernels."""
+    T, d = 50, 128
+    L = synth.moe_layer(T, d, N, 64, dtype="bf16", seed=N)
+    L.W_router[1::2] = L.W_router[0:N - 1:2][: len(L.W_router[1::2])]
+    L.x[7] = 0.0
+    x, Wr = to_gpu(L.x, BF), to_gpu(L.W_router, BF)
+    k, ids, w, lg = B.elb_router_route(x, Wr, K=K, with_logits=True)
+    k2, ids2, w2 = B.elb_route(lg, K=K)
+    torch.cuda.synchronize()
+    assert int(k[7]) == 1 and int(ids[7, 0]) == 0
+    assert torch.equal(k, k2) and torch.equal(ids, ids2) and torch.equal(w, w2)
