@@ -26,19 +26,36 @@ namespace elb {
 
 namespace {
 
+// The expert e that owns item `item` of a numbering in which expert e's items are
+// [per tile_off[e], per tile_off[e + 1]): every lane looks at one expert (N <= 64), so it takes
+// one memory round trip instead of a binary search's six.  first: e's first item; tiles, row0,
+// end: its M-tiles, first row and row past its last one.
+__device__ __forceinline__ void find_expert(const int* __restrict__ tile_off,
+                                            const int* __restrict__ offsets, int N, int item,
+                                            int per, int& e, int& first, int& tiles, int& row0,
+                                            int& end) {
+    const int lane = threadIdx.x & 63;
+    const int l = lane < N ? lane : N - 1;
+    const int t0 = tile_off[l], t1 = tile_off[l + 1];
+    const int r0 = offsets[l], r1 = offsets[l + 1];
+    const uint64_t mine = __ballot(lane < N && t0 * per <= item && item < t1 * per);
+    e = __builtin_ctzll(mine | (1ull << 63));
+    first = __builtin_amdgcn_readlane(t0, e) * per;
+    tiles = __builtin_amdgcn_readlane(t1, e) - __builtin_amdgcn_readlane(t0, e);
+    row0 = __builtin_amdgcn_readlane(r0, e);
+    end = __builtin_amdgcn_readlane(r1, e);
+}
+
+// M-tile `tile` (tile_rows rows): its expert e, first row, rows; alone: e has no other tile
 __device__ __forceinline__ void find_tile(const int* __restrict__ tile_off,
                                           const int* __restrict__ offsets, int N, int tile,
-                                          int tile_rows, int& e, int& row0, int& rows) {
-    int lo = 0, hi = N - 1;  // largest e with tile_off[e] <= tile
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tile_off[mid] <= tile) lo = mid;
-        else hi = mid - 1;
-    }
-    e = lo;
-    row0 = offsets[e] + (tile - tile_off[e]) * tile_rows;
-    const int end = offsets[e + 1];
+                                          int tile_rows, int& e, int& row0, int& rows,
+                                          bool& alone) {
+    int first, tiles, end;
+    find_expert(tile_off, offsets, N, tile, 1, e, first, tiles, row0, end);
+    row0 += (tile - first) * tile_rows;
     rows = end - row0 < tile_rows ? end - row0 : tile_rows;
+    alone = tiles == 1;
 }
 
 // silu(z) = z / (1 + e^-z), with a hardware reciprocal (the result is rounded to bf16 or
@@ -311,18 +328,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // block -> (expert, N-tile, M-tile innermost), XCD-contiguous (xcd_tile with one column)
     int L, unused;
     if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, 1, L, unused)) return;
-    int lo = 0, hi = N - 1;  // largest e with tile_off[e] nt_count <= L
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tile_off[mid] * nt_count <= L) lo = mid;
-        else hi = mid - 1;
-    }
-    const int e = lo;
-    const int tiles = tile_off[e + 1] - tile_off[e];
-    const int local = L - tile_off[e] * nt_count;
-    const int ntile = local / tiles;
-    const int row0 = offsets[e] + (local - ntile * tiles) * BM;
-    const int left = offsets[e + 1] - row0;
+    int e, first, tiles, row0, end;
+    find_expert(tile_off, offsets, N, L, nt_count, e, first, tiles, row0, end);
+    const int ntile = (L - first) / tiles;
+    row0 += (L - first - ntile * tiles) * BM;
+    const int left = end - row0;
     const int rot = (int)((int64_t)ntile * (((MODE == 0) ? d : m) / 64) / nt_count);
     if (left <= 64)
         gemm_mid_body<MODE, 64, BN, 2>(A, row_token, B, e, row0, left, ntile, rot, d, m, C, sm,
@@ -421,13 +431,14 @@ __device__ __forceinline__ void tail_block(const bf16_t* __restrict__ A,
     else tail_task<MODE, 2>(wp, xp, s0, s1, rows, row0, out_ld, out_col, C, lds);
 }
 
-// NTW: the weight copies carry the non-temporal hint (the kernel below picks it by size)
-template <int MODE, bool NTW>
-__device__ __forceinline__ void gemm_dma_body(
-    const bf16_t* __restrict__ A, const int* __restrict__ row_token,
-    const bf16_t* __restrict__ B, const int* __restrict__ offsets,
-    const int* __restrict__ tile_off, const int* __restrict__ tail_list, int big_blocks,
-    int N, int d, int m, bf16_t* __restrict__ C, char* sm_bytes) {
+// One 256 x 256 tile.  NTW: the weight copies carry the non-temporal hint (the kernel below picks it
+// by size); ROT: the contraction starts at its k-tile rot (see the pipeline), else at 0.
+template <int MODE, bool NTW, bool ROT>
+__device__ __forceinline__ void gemm_dma_tile(const bf16_t* __restrict__ A,
+                                              const int* __restrict__ row_token,
+                                              const bf16_t* __restrict__ B, int e, int ntile,
+                                              int row0, int rows, int rot, int d, int m,
+                                              bf16_t* __restrict__ C, char* sm_bytes) {
     constexpr int TM = 256, TN = 256, TK = 64;
     constexpr int UNIT = TM * TK;  // elements of one ring unit: the A or the B half of a k-tile
     constexpr int NU = 5;          // units in the ring
@@ -435,38 +446,7 @@ __device__ __forceinline__ void gemm_dma_body(
     constexpr int PITCH = OUTC * 2 + 16;          // bytes per row of the staged output tile
     static_assert(TM == TN && TM * PITCH <= NU * UNIT * 2, "staging tile exceeds LDS");
     bf16_t* const sm = reinterpret_cast<bf16_t*>(sm_bytes);
-    if ((int)blockIdx.x >= big_blocks) {  // the remainder blocks after the tiles
-        tail_block<MODE>(A, row_token, B, offsets, tail_list, (int)blockIdx.x - big_blocks, d,
-                         m, TM, C, sm_bytes);
-        return;
-    }
-
-    const int nt_count = (MODE == 0) ? m / 128 : (d + TN - 1) / TN;
-    int tile, ntile;
-    if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
-    int e, row0, rows;
-    find_tile(tile_off, offsets, N, tile, TM, e, row0, rows);
-
     const int Kd = (MODE == 0) ? d : m;
-    const bool alone = tile_off[e + 1] - tile_off[e] == 1;
-    const int rot = alone && (ntile & 1) ? Kd / TK / 2 : 0;  // see the pipeline below
-    // An expert's last tile with at most 128 rows: the smaller tile forms of the mid-sized kernel,
-    // as wide as this one's, 3 x (16 + 32) KB of LDS at most (64 rows: per k-tile 40 KB copied and
-    // 64 KB read instead of 64 and 128, and a quarter of the MFMAs).  OLMoE-shaped layer, us:
-    // 2300 tokens 380 -> 360, 8192 tokens top-8 950 -> 907, 16384 tokens 1603 -> 1572; the sizes
-    // without such tiles as before.  Taken in order: all of them after the full tiles would
-    // balance the units better, but reads their experts' weights from HBM again (3000 tokens 391
-    // -> 439, 4096 top-8 496 -> 490).
-    if (rows <= 128) {
-        if (rows <= 64)
-            gemm_mid_body<MODE, 64, TN, 1>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
-                                           sm_bytes, NTW);
-        else
-            gemm_mid_body<MODE, 128, TN, 2>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
-                                            sm_bytes, NTW);
-        return;
-    }
-
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wid = tid >> 6;
@@ -600,7 +580,10 @@ __device__ __forceinline__ void gemm_dma_body(
     // the rows of every point in use have to fit there.  With more M-tiles, where the weights are
     // shared too, all blocks stay in step (4096 tokens with 8 points: 447 -> 466 us).
     const int nk = Kd / TK;  // >= 1
-    auto k_of = [&](int t) { return (t + rot < nk ? t + rot : t + rot - nk) * TK; };
+    auto k_of = [&](int t) {
+        if (!ROT) return t * TK;
+        return (t + rot < nk ? t + rot : t + rot - nk) * TK;
+    };
     // as if barriers at t = -3, -2, -1 had issued B(0); A(0), B(1); A(1), B(2)
     issue(Bblk, b_off, 0, k_of(0), NTW);
     issue(Ablk, a_off, 1, k_of(0), false);
@@ -718,6 +701,52 @@ __device__ __forceinline__ void gemm_dma_body(
     }
 }
 
+template <int MODE, bool NTW>
+__device__ __forceinline__ void gemm_dma_body(
+    const bf16_t* __restrict__ A, const int* __restrict__ row_token,
+    const bf16_t* __restrict__ B, const int* __restrict__ offsets,
+    const int* __restrict__ tile_off, const int* __restrict__ tail_list, int big_blocks,
+    int N, int d, int m, bf16_t* __restrict__ C, char* sm_bytes) {
+    constexpr int TM = 256, TN = 256, TK = 64;
+    if ((int)blockIdx.x >= big_blocks) {  // the remainder blocks after the tiles
+        tail_block<MODE>(A, row_token, B, offsets, tail_list, (int)blockIdx.x - big_blocks, d,
+                         m, TM, C, sm_bytes);
+        return;
+    }
+
+    const int nt_count = (MODE == 0) ? m / 128 : (d + TN - 1) / TN;
+    int tile, ntile;
+    if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
+    int e, row0, rows;
+    bool alone;
+    find_tile(tile_off, offsets, N, tile, TM, e, row0, rows, alone);
+
+    const int Kd = (MODE == 0) ? d : m;
+    const int rot = alone && (ntile & 1) ? Kd / TK / 2 : 0;  // see the pipeline below
+    // An expert's last tile with at most 128 rows: the smaller tile forms of the mid-sized kernel,
+    // as wide as this one's, 3 x (16 + 32) KB of LDS at most (64 rows: per k-tile 40 KB copied and
+    // 64 KB read instead of 64 and 128, and a quarter of the MFMAs).  OLMoE-shaped layer, us:
+    // 2300 tokens 380 -> 360, 8192 tokens top-8 950 -> 907, 16384 tokens 1603 -> 1572; the sizes
+    // without such tiles as before.  Taken in order: all of them after the full tiles would
+    // balance the units better, but reads their experts' weights from HBM again (3000 tokens 391
+    // -> 439, 4096 top-8 496 -> 490).
+    if (rows <= 128) {
+        if (rows <= 64)
+            gemm_mid_body<MODE, 64, TN, 1>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
+                                           sm_bytes, NTW);
+        else
+            gemm_mid_body<MODE, 128, TN, 2>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
+                                            sm_bytes, NTW);
+        return;
+    }
+    if (rot)  // (a form of its own: the wrap cost the loop 0.5 % at 4096 tokens)
+        gemm_dma_tile<MODE, NTW, true>(A, row_token, B, e, ntile, row0, rows, rot, d, m, C,
+                                       sm_bytes);
+    else
+        gemm_dma_tile<MODE, NTW, false>(A, row_token, B, e, ntile, row0, rows, 0, d, m, C,
+                                        sm_bytes);
+}
+
 template <int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_bf16_dma(
     const bf16_t* __restrict__ A, const int* __restrict__ row_token,
@@ -767,7 +796,8 @@ __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
     int tile, ntile;
     if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
     int e, row0, rows;
-    find_tile(tile_off, offsets, N, tile, FBM, e, row0, rows);
+    bool alone;
+    find_tile(tile_off, offsets, N, tile, FBM, e, row0, rows, alone);
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wid >> 1, wn = wid & 1;
