@@ -77,8 +77,11 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
     if (t0 < T) rows = (int)((T - t0) < kWave ? (T - t0) : kWave);
     stage_rows<NP, FULL>(logits + t0 * N, N, rows, vec4, tile, lane);
     __syncthreads();
-    // lanes past the last token route a copy of the first one and write nothing: every lane
-    // takes part in the staged stores at the end (no barrier follows)
+    // a wave with no token of its own must not read draws (token t0 lies past the last one); no
+    // barrier follows
+    if (rows == 0) return;
+    // lanes past the last token route a copy of the wave's first one and write nothing: every
+    // lane takes part in the staged stores at the end
     const bool active = lane < rows;
     const float* row = tile + (active ? lane : 0) * LD;
     const int64_t t = t0 + (active ? lane : 0);

@@ -250,3 +250,20 @@ def test_tail_random_tied_and_neg_inf_logits(N, K):
     for renorm in (False, True):
         _check_tail(lg, rand, K, renorm, "tied/-inf logits N=%d K=%d renorm=%d"
                     % (N, K, renorm))
+
+
+@pytest.mark.parametrize("T,N,K", [(1, 64, 8), (65, 64, 16), (63, 37, 8), (200, 5, 3), (70, 64, 20)])
+def test_tail_random_draws_end_their_buffer(T, N, K):
+    """Logits and draws that end a whole device allocation, with waves of the last block past the
+    last token: nothing past them is read."""
+    lg = synth.planted_logits(T, N, seed=T, m_max=min(8, N))
+    rand = synth.uniform_draws(T, N, seed=T)
+    bufs = [torch.empty(3 << 20, dtype=torch.float32, device="cuda") for _ in range(2)]  # 12 MiB
+    views = [b[-T * N:].view(T, N) for b in bufs]
+    views[0].copy_(torch.from_numpy(lg))
+    views[1].copy_(torch.from_numpy(rand))
+    k, ids, w = B.elb_route_tail_random(views[0], views[1], K=K)
+    k2, ids2, w2 = B.elb_route_tail_random(to_gpu(lg), to_gpu(rand), K=K)
+    torch.cuda.synchronize()
+    assert torch.equal(k, k2) and torch.equal(ids, ids2) and torch.equal(w, w2)
+    _check_tail(lg, rand, K)
