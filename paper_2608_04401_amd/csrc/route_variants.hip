@@ -9,6 +9,8 @@
 // u_i = exp(l_(i) - l_(0)) in rank order (rel_exp), S as the same tree over the ranks
 // (tree_sum), the same E_i and first argmin, w = u * (1 / denominator).  The elbow angle (no
 // selection asked for) and tail randomisation with K <= 16 sort the keys only.
+#include <cfloat>
+
 #include "route_lane.h"
 
 namespace elb {
@@ -56,12 +58,40 @@ __device__ __forceinline__ void first_k_experts(const float (&key)[NP], const fl
     selected_in_id_order<NP, KM>(taken, [&](int c) { return order_key(row[c]); }, k, cid, ck);
 }
 
+// The KM largest of v[0 .. NP) into v[0 .. KM), descending (the rest is left in no order): groups
+// of KM sorted by the network, then folded into the first, group by group: the larger of a_i and
+// b_(KM - 1 - i) are the KM largest of two descending groups, in a bitonic order that log2(KM)
+// stages of comparators sort.  528 min/max for the 8 largest of 64 and 744 for the 16 largest,
+// where K - k passes over the draws, each a masked minimum with its index, took some 450
+// instructions each (65536 tokens, N = 64, K = 8: angle and tail randomisation 35.7 -> 25.9 us).
+template <int NP, int KM>
+__device__ __forceinline__ void largest_desc(float (&v)[NP]) {
+#pragma unroll
+    for (int g = 0; g < NP; g += KM)
+        sort_desc<KM>(v + g, std::make_integer_sequence<int, NetHolder<KM>::net.n>{});
+#pragma unroll
+    for (int g = KM; g < NP; g += KM) {
+#pragma unroll
+        for (int i = 0; i < KM; ++i) v[i] = fmaxf(v[i], v[g + KM - 1 - i]);
+#pragma unroll
+        for (int o = KM / 2; o >= 1; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < KM; ++i)
+                if (!(i & o)) {
+                    const float hi = fmaxf(v[i], v[i + o]), lo = fminf(v[i], v[i + o]);
+                    v[i] = hi;
+                    v[i + o] = lo;
+                }
+    }
+}
+
 // PAIRS: sort (key, id) pairs (a selection with any cap is asked for).  Otherwise the keys
 // alone are sorted (the routing kernel's value network: the same sorted keys, so the same e
 // and theta bits, at two instructions per comparator): for the elbow angle (no selection), and
 // for tail randomisation with K <= kLaneMaxK, whose first k experts are then recovered by the
 // routing kernel's selection rule.
-template <int NP, bool FULL, bool PAIRS>
+// KMAX (keys alone): a bound on K, 8 or kLaneMaxK
+template <int NP, bool FULL, bool PAIRS, int KMAX>
 __global__ __launch_bounds__(256) void route_pair_kernel(
     const float* __restrict__ logits, const float* __restrict__ rand, int64_t T, int N, int K,
     float eps, int mode, int renorm, int vec4, XTable xt, int* __restrict__ kout,
@@ -86,6 +116,23 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
     const float* row = tile + (active ? lane : 0) * LD;
     const int64_t t = t0 + (active ? lane : 0);
     const int Nn = FULL ? NP : N;
+
+    // tail randomisation from sorted keys: the lane's draws, loaded before the sort, which they
+    // arrive behind (16-byte loads where every row starts on a 16-byte boundary)
+    float draw[NP];
+    if (!PAIRS && rand) {
+        const float* const rr = rand + t * N;
+        if (FULL && ((uintptr_t)rand % 16) == 0) {
+#pragma unroll
+            for (int c = 0; c < NP; c += 4) {
+                const float4 q = *reinterpret_cast<const float4*>(rr + c);
+                draw[c] = q.x; draw[c + 1] = q.y; draw[c + 2] = q.z; draw[c + 3] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < NP; ++c) draw[c] = (c < Nn) ? rr[c] : INFINITY;
+        }
+    }
 
     // ---- sort (key, id) pairs: rank r holds key[r] and id[r] ----
     float key[NP];
@@ -158,9 +205,10 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
     if (!PAIRS) {
         // tail randomisation with K <= kLaneMaxK from the sorted keys alone: the first k ranks'
         // experts by the routing kernel's selection rule, then the K - k untaken experts with
-        // the smallest draws (equal draws: lower id), as below; the same ids and weight bits
-        // as the pair path (an elbow expert's u is recomputed from its own key)
-        constexpr int KM = NP < kLaneMaxK ? NP : kLaneMaxK;
+        // the smallest draws (equal draws: lower id) by the same rule on the negated draws; the
+        // same ids and weight bits as the pair path (an expert's u is recomputed from its own
+        // key)
+        constexpr int KM = NP < KMAX ? NP : KMAX;
         float okey[NP];
 #pragma unroll
         for (int c = 0; c < NP; ++c) okey[c] = (c < Nn) ? order_key(row[c]) : -INFINITY;
@@ -168,33 +216,69 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
         int cid[KM];
         float ck[KM];
         first_k_experts<NP, KM>(key, okey, row, Nn, k, taken, cid, ck);
-        const float* rr = rand + t * N;
-        float draw[NP];
+        float dkey[NP], top[NP];  // negated draws (-inf: taken or past N), the KM largest sorted
 #pragma unroll
-        for (int c = 0; c < NP; ++c) draw[c] = (c < Nn) ? rr[c] : INFINITY;
+        for (int c = 0; c < NP; ++c) {
+            // order_key: a draw of 0 gives +0; the bound keeps an infinite draw above the taken
+            const float q = fmaxf(order_key(-draw[c]), -FLT_MAX);
+            dkey[c] = (c < Nn && !((taken >> c) & 1ull)) ? q : -INFINITY;
+            top[c] = dkey[c];
+        }
+        largest_desc<NP, KM>(top);
+        const int n_tail = K - k;  // 0 .. KM - 1
+        uint64_t sel = select_first_k<NP, KM>(
+            top, [&](int c) { return dkey[c]; }, Nn, n_tail > 0 ? n_tail : 1);
+        if (n_tail == 0) sel = 0;
+        int did[KM];
+        float dk[KM];
+        selected_in_id_order<NP, KM>(
+            sel,
+            [&](int c) {  // (c may be NP - 1 where no bit is left)
+                return fmaxf(order_key(-rand[t * N + (c < Nn ? c : Nn - 1)]), -FLT_MAX);
+            },
+            n_tail, did, dk);
+        // the tail in its order: tail[j] for j < n_tail
+        int tail[KM];
+        bool distinct = true;
+#pragma unroll
+        for (int j = 0; j + 1 < KM; ++j)
+            if (j + 1 < n_tail && top[j] == top[j + 1]) distinct = false;
+        if (__builtin_expect(__all(distinct), 1)) {
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                tail[j] = did[0];
+#pragma unroll
+                for (int q = 0; q < KM; ++q) tail[j] = (dk[q] == top[j]) ? did[q] : tail[j];
+            }
+        } else {  // by counting (equal draws: lower id, i.e. lower position, first)
+            int rank[KM];
+#pragma unroll
+            for (int q = 0; q < KM; ++q) {
+                rank[q] = q < n_tail ? 0 : KM;
+#pragma unroll
+                for (int o = 0; o < KM; ++o)
+                    if (o != q && o < n_tail && (o < q ? dk[o] >= dk[q] : dk[o] > dk[q]))
+                        ++rank[q];
+            }
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                tail[j] = did[0];
+#pragma unroll
+                for (int q = 0; q < KM; ++q) tail[j] = (rank[q] == j) ? did[q] : tail[j];
+            }
+        }
+        float tu[KM];
+#pragma unroll
+        for (int j = 0; j < KM; ++j) tu[j] = rel_exp(order_key(row[tail[j]]), nl);
         float denom = S;
         if (renorm) {
             float sel_u[KM];
 #pragma unroll
             for (int j = 0; j < KM; ++j) sel_u[j] = j < k ? u[j] : 0.f;
             denom = tree_sum<KM>(sel_u);
-        }
-        for (int j = k; j < K; ++j) {
-            float bv = INFINITY;
-            int bc = -1;
 #pragma unroll
-            for (int c = 0; c < NP; ++c) {
-                const bool ok = c < Nn && !((taken >> c) & 1ull) && (bc < 0 || draw[c] < bv);
-                bv = ok ? draw[c] : bv;
-                bc = ok ? c : bc;
-            }
-            taken |= 1ull << bc;
-            const float ub = rel_exp(order_key(row[bc]), nl);
-            if (active) {
-                ids[t * K + j] = bc;
-                wout[t * K + j] = ub;
-            }
-            if (renorm) denom += ub;
+            for (int j = 0; j < KM; ++j)
+                if (j < n_tail) denom += tu[j];
         }
         const float inv = 1.0f / denom;
         if (!active) return;
@@ -212,7 +296,13 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
                 wout[t * K + rank] = rel_exp(ck[r], nl) * inv;
             }
         }
-        for (int j = k; j < K; ++j) wout[t * K + j] *= inv;  // this lane's own writes
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+            if (j < n_tail) {
+                ids[t * K + k + j] = tail[j];
+                wout[t * K + k + j] = tu[j] * inv;
+            }
+        }
         return;
     }
 
@@ -313,11 +403,15 @@ void launch_pair_np(const float* logits, const float* rand, int64_t T, int N,
     // keys only: the elbow angle (no ids), or tail randomisation with K <= kLaneMaxK
     const bool keys_only = !ids || (rand && p.K <= kLaneMaxK);
     if (!keys_only)
-        ELB_LAUNCH((route_pair_kernel<NP, FULL, true>), grid, dim3(256), 0, s, logits,
+        ELB_LAUNCH((route_pair_kernel<NP, FULL, true, NP>), grid, dim3(256), 0, s, logits,
                            rand, T, N, p.K, p.eps, p.mode, p.renormalize, vec4, make_xtable(N),
                            k, ids, w, e, theta);
+    else if (ids && p.K > 8)
+        ELB_LAUNCH((route_pair_kernel<NP, FULL, false, kLaneMaxK>), grid, dim3(256), 0, s,
+                           logits, rand, T, N, p.K, p.eps, p.mode, p.renormalize, vec4,
+                           make_xtable(N), k, ids, w, e, theta);
     else
-        ELB_LAUNCH((route_pair_kernel<NP, FULL, false>), grid, dim3(256), 0, s, logits,
+        ELB_LAUNCH((route_pair_kernel<NP, FULL, false, 8>), grid, dim3(256), 0, s, logits,
                            rand, T, N, p.K, p.eps, p.mode, p.renormalize, vec4,
                            make_xtable(N), k, ids, w, e, theta);
 }
