@@ -606,8 +606,7 @@ __device__ __forceinline__ void gemm_dma_tile(const bf16_t* __restrict__ A,
     for (; t < nk - 1; ++t) {
         const int ub1 = ub + 2 >= NU ? ub + 2 - NU : ub + 2;  // units of tile t + 1
         const int ua1 = ua + 2 >= NU ? ua + 2 - NU : ua + 2;
-        const int ka = __builtin_amdgcn_readfirstlane(k_of(t + 2));
-        const int kb = __builtin_amdgcn_readfirstlane(k_of(t + 3));
+        const int ka = k_of(t + 2), kb = k_of(t + 3);
         load(fa1, fb1, ua, ub, 1);
         mma(fa0, fb0, true);
         load(fa0, fb0, ua, ub, 2);
