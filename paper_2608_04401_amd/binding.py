@@ -8,6 +8,7 @@ if the library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import Optional
 
@@ -95,11 +96,13 @@ def _check(fn: str, status: int):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle.  (torch.cuda.current_stream() builds a Stream object first:
+    2.8 us of a call's 10 to 19.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -125,7 +128,7 @@ _ws_cache: dict = {}
 
 def workspace(nbytes: int, device) -> torch.Tensor:
     """A cached uint8 device buffer of at least nbytes (one per device)."""
-    key = torch.device(device).index
+    key = device.index if isinstance(device, torch.device) else torch.device(device).index
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         buf = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
@@ -230,6 +233,7 @@ def elb_dispatch(k: torch.Tensor, ids: torch.Tensor, N: int):
     return counts, offsets, row_token, inv
 
 
+@functools.lru_cache(maxsize=256)
 def elb_moe_workspace_bytes(T: int, d: int, N: int, m: int, K: int, dtype: int) -> int:
     return int(lib().elb_moe_workspace_bytes(T, d, N, m, K, dtype))
 
