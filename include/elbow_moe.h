@@ -198,9 +198,9 @@ int elb_moe_experts(const void *x, const void *W_gate_up, const void *W_down,
 
 /*
  * The whole layer: elb_router_logits and elb_route (fused as in elb_router_route for bf16 and
- * K <= 16; with N = 64 the router's contraction is split into four quarters, whose partial
- * logits are summed in a fixed order before the routing -- one launch up to 4096 tokens when
- * d % 256 == 0, two above or for other d; every form gives the same bits), then
+ * K <= 16: one launch up to 4096 tokens; above, two launches when N = 64 and d % 256 == 0, the
+ * router's contraction in four quarters whose partial logits are summed in a fixed order
+ * before the routing, else one; every form gives the same bits), then
  * elb_moe_experts, on one stream, with no host round trip.  Arguments as above; the optional debug outputs (NULL to
  * skip) receive the intermediate results of this call:
  *   logits_out [T, N] float, k_out [T], ids_out [T, K], w_out [T, K],
