@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import functools
 import os
+import threading
 from typing import Optional
 
 import torch
@@ -123,16 +124,35 @@ def _dev(*ts):
             raise ValueError("tensors must be contiguous")
 
 
-_ws_cache: dict = {}
+_ws = threading.local()  # .pool: {(device index, stream handle): buffer}
+_WS_STREAMS = 8          # buffers a thread keeps
 
 
-def workspace(nbytes: int, device) -> torch.Tensor:
-    """A cached uint8 device buffer of at least nbytes (one per device)."""
-    key = device.index if isinstance(device, torch.device) else torch.device(device).index
-    buf = _ws_cache.get(key)
+def workspace(nbytes: int, device, stream: Optional[int] = None) -> torch.Tensor:
+    """Scratch of at least nbytes for one call on `stream` (None: the current one).
+
+    A thread keeps one uint8 buffer per device and stream (the last _WS_STREAMS of them, until
+    the thread ends): calls in order on one stream may share scratch, calls that can overlap, on
+    other streams or from other threads, must not.  A buffer is allocated and used on one stream
+    only, so one that is dropped (replaced by a larger one, or the oldest of too many) is safe
+    with the allocator, which hands it on in that stream's order.  Under graph capture nothing
+    is kept: the scratch then comes from the graph's own memory pool, which no call outside the
+    graph uses and which lasts as long as the graph can be replayed."""
+    nbytes = max(int(nbytes), 1)
+    if torch._C._cuda_isCurrentStreamCapturing():
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    try:
+        pool = _ws.pool
+    except AttributeError:
+        pool = _ws.pool = {}
+    index = device.index if isinstance(device, torch.device) else torch.device(device).index
+    key = (index, _stream() if stream is None else stream)
+    buf = pool.get(key)
     if buf is None or buf.numel() < nbytes:
-        buf = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=device)
-        _ws_cache[key] = buf
+        pool.pop(key, None)
+        if len(pool) >= _WS_STREAMS:
+            del pool[next(iter(pool))]
+        buf = pool[key] = torch.empty(nbytes, dtype=torch.uint8, device=device)
     return buf
 
 
@@ -226,10 +246,11 @@ def elb_dispatch(k: torch.Tensor, ids: torch.Tensor, N: int):
     row_token = torch.full((T * K,), -1, dtype=torch.int32, device=dev)
     inv = torch.empty((T, K), dtype=torch.int32, device=dev)
     nb = lib().elb_dispatch_workspace_bytes(T, N)
-    ws = workspace(nb, dev)
+    stream = _stream()
+    ws = workspace(nb, dev, stream)
     _check("elb_dispatch", lib().elb_dispatch(_ptr(k), _ptr(ids), T, N, K, _ptr(counts),
                                               _ptr(offsets), _ptr(row_token), _ptr(inv),
-                                              _ptr(ws), ws.numel(), _stream()))
+                                              _ptr(ws), ws.numel(), stream))
     return counts, offsets, row_token, inv
 
 
@@ -262,15 +283,16 @@ def elb_moe_experts(x, W_gate_up, W_down, k, ids, w, residual=None, out=None,
     dt = _dtype_code(x)
     y = torch.empty_like(x) if out is None else out
     nb = elb_moe_workspace_bytes(T, d, N, m, K, dt)
-    ws = workspace(nb, x.device)
+    stream = _stream()
+    ws = workspace(nb, x.device, stream)
     if packed is None:
         _check("elb_moe_experts", lib().elb_moe_experts(
             _ptr(x), _ptr(W_gate_up), _ptr(W_down), _ptr(k), _ptr(ids), _ptr(w),
-            _ptr(residual), T, d, N, m, K, dt, _ptr(y), _ptr(ws), ws.numel(), _stream()))
+            _ptr(residual), T, d, N, m, K, dt, _ptr(y), _ptr(ws), ws.numel(), stream))
     else:
         _check("elb_moe_experts_packed", lib().elb_moe_experts_packed(
             _ptr(x), _ptr(W_gate_up), _ptr(W_down), _ptr(packed), _ptr(k), _ptr(ids), _ptr(w),
-            _ptr(residual), T, d, N, m, K, dt, _ptr(y), _ptr(ws), ws.numel(), _stream()))
+            _ptr(residual), T, d, N, m, K, dt, _ptr(y), _ptr(ws), ws.numel(), stream))
     return y
 
 
@@ -287,7 +309,8 @@ def elb_moe_forward(x, W_router, W_gate_up, W_down, K: int = 8, eps: float = 1e-
     dev = x.device
     y = torch.empty_like(x) if out is None else out
     nb = elb_moe_workspace_bytes(T, d, N, m, K, dt)
-    ws = workspace(nb, dev)
+    stream = _stream()
+    ws = workspace(nb, dev, stream)
     dbg = {}
     if debug:
         dbg = {"logits": torch.empty((T, N), dtype=torch.float32, device=dev),
@@ -297,7 +320,7 @@ def elb_moe_forward(x, W_router, W_gate_up, W_down, K: int = 8, eps: float = 1e-
                "counts": torch.empty(N, dtype=torch.int32, device=dev)}
     p = RouteParams(K, eps, mode, int(renormalize))
     tail = (_ptr(dbg.get("logits")), _ptr(dbg.get("k")), _ptr(dbg.get("ids")),
-            _ptr(dbg.get("w")), _ptr(dbg.get("counts")), _stream())
+            _ptr(dbg.get("w")), _ptr(dbg.get("counts")), stream)
     if packed is None:
         _check("elb_moe_forward", lib().elb_moe_forward(
             _ptr(x), _ptr(W_router), _ptr(W_gate_up), _ptr(W_down), _ptr(residual), T, d, N, m,
@@ -343,7 +366,8 @@ def elb_moe_forward_prepared(x, W_router, W_gate_up, W_down, K: int = 8, eps: fl
                              out=None, packed=None):
     """elb_moe_forward with its arguments marshalled once: returns (call, y), where call() enqueues
     the layer on the stream that was current here and raises on a failed status.  For timing
-    loops, where the per-call argument checks would otherwise add host time."""
+    loops, where the per-call argument checks would otherwise add host time.  call() uses the
+    scratch of this thread and stream, so it is for the thread that prepared it."""
     _dev(x, W_router, W_gate_up, W_down, residual, out, packed)
     T, d = x.shape
     N = W_router.shape[0]

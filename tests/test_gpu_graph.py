@@ -2,8 +2,8 @@
 replayed.  No entry point allocates, synchronises or records a memset, so a captured call is
 the same kernel sequence as an eager one: every replay must give the eager result bit for
 bit.  Between replays the static input is overwritten in place and eager layer calls on
-other inputs run on the same stream (they reuse the workspace the graph was captured with),
-so each replay is checked against a fresh eager call on the new input.
+other inputs run on the same stream (on their own workspace: the graph's lies in its memory
+pool), and each replay is checked against a fresh eager call on the new input.
 
 Cases cover each path the forward takes by size: the OLMoE-shaped prefill layer (split
 router, histogram-fed dispatch, large-tile GEMMs with remainder blocks), the decode-sized
