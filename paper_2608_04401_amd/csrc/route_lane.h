@@ -52,6 +52,17 @@ struct PhasedHolder {
 // -0 into +0), so that min/max compile to single v_min_f32/v_max_f32.  Non-NaN inputs.
 __device__ __forceinline__ float order_key(float f) { return f + 0.0f; }
 
+// order_key of any bits: a NaN counts as -inf.  No result is promised for a NaN logit, but with
+// every key ordered the k selected experts are k different ones below N, so that a histogram
+// taken from the selection counts what the dispatch finds in ids (a surplus count would leave
+// rows of the expert lists unwritten).  For the kernels that take one, and where pads take part
+// in the sort; a token by 16 lanes has 4 keys a lane, so it costs nothing there.  (An integer
+// test, because one file is built without NaN semantics.)
+__device__ __forceinline__ float order_key_any(float f) {
+    const int i = __float_as_int(f);
+    return order_key(__int_as_float((i & 0x7fffffff) > 0x7f800000 ? (int)0xff800000 : i));
+}
+
 // One comparator of the network: larger value to the lower position (v_max_f32/v_min_f32).
 template <int NP, int Q>
 __device__ __forceinline__ void compare_exchange(float* key) {
@@ -280,12 +291,12 @@ __device__ __forceinline__ uint64_t select_first_k(const float (&key)[NP], OKey&
 // The k selected experts (select_first_k) in increasing id order, with their keys: cid[r],
 // ck[r] for r < k; ck = -inf (and cid a valid id) for k <= r < KM.  key_of(c): expert c's key
 // re-read from memory (c is not a compile-time constant there).
-template <int NP, int KM, class KeyOf>
-__device__ __forceinline__ void selected_in_id_order(uint64_t sel, KeyOf&& key_of, int k,
+template <int KM, class KeyOf>
+__device__ __forceinline__ void selected_in_id_order(uint64_t sel, KeyOf&& key_of, int Nn, int k,
                                                      int (&cid)[KM], float (&ck)[KM]) {
 #pragma unroll
     for (int r = 0; r < KM; ++r) {
-        const int b = lowest_bit_or(sel, NP - 1);  // r >= k: no bit left, a valid id
+        const int b = lowest_bit_or(sel, Nn - 1);  // r >= k: no bit left, a valid id
         const float kb = key_of(b);                // read on every lane: no branch
         cid[r] = b;
         ck[r] = r < k ? kb : -INFINITY;
@@ -308,7 +319,7 @@ __device__ __forceinline__ void select_emit(const float (&key)[NP], OKey&& okey,
     const uint64_t sel = select_first_k<NP, KM>(key, okey, Nn, k, &tau);
     int cid[KM];
     float ck[KM];
-    selected_in_id_order<NP, KM>(sel, key_of, k, cid, ck);
+    selected_in_id_order<KM>(sel, key_of, Nn, k, cid, ck);
     float denom = S;
     if (renorm) {
         float sel_u[KM];
@@ -456,7 +467,7 @@ __device__ __forceinline__ void route_token_x16(float* row, int N, int K, float 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int c = 4 * sl + i;
-        v[i] = ((int64_t)ord_flip32(__float_as_int(order_key(row[c]))) << 32) |
+        v[i] = ((int64_t)ord_flip32(__float_as_int(order_key_any(row[c]))) << 32) |
                (uint32_t)(NP - 1 - c);
     }
     // ---- bitonic sort, descending: position p = 4 sl + i ----

@@ -55,7 +55,7 @@ __device__ __forceinline__ void first_k_experts(const float (&key)[NP], const fl
                                                 uint64_t& taken, int (&cid)[KM],
                                                 float (&ck)[KM]) {
     taken = select_first_k<NP, KM>(key, [&](int c) { return okey[c]; }, Nn, k);
-    selected_in_id_order<NP, KM>(taken, [&](int c) { return order_key(row[c]); }, k, cid, ck);
+    selected_in_id_order<KM>(taken, [&](int c) { return order_key(row[c]); }, Nn, k, cid, ck);
 }
 
 // The KM largest of v[0 .. NP) into v[0 .. KM), descending (the rest is left in no order): groups
@@ -231,12 +231,9 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
         if (n_tail == 0) sel = 0;
         int did[KM];
         float dk[KM];
-        selected_in_id_order<NP, KM>(
-            sel,
-            [&](int c) {  // (c may be NP - 1 where no bit is left)
-                return fmaxf(order_key(-rand[t * N + (c < Nn ? c : Nn - 1)]), -FLT_MAX);
-            },
-            n_tail, did, dk);
+        selected_in_id_order<KM>(
+            sel, [&](int c) { return fmaxf(order_key(-rand[t * N + c]), -FLT_MAX); }, Nn, n_tail,
+            did, dk);
         // the tail in its order: tail[j] for j < n_tail
         int tail[KM];
         bool distinct = true;

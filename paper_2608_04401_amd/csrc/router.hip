@@ -320,7 +320,7 @@ __global__ __launch_bounds__(64) void route_split_sum(const float* __restrict__ 
     }
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
-        okey[c] = order_key(okey[c]);
+        okey[c] = order_key_any(okey[c]);
         key[c] = okey[c];
     }
     sort_desc<NP>(key, std::make_integer_sequence<int, NetHolder<NP>::net.n>{});
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(64) void route_split_sum(const float* __restrict__ 
         ow[q] = 0.f;
     }
     select_emit<NP, true, KMAX>(
-        key, [&](int c) { return okey[c]; }, [&](int c) { return order_key(logit(c)); }, NP, K,
+        key, [&](int c) { return okey[c]; }, [&](int c) { return order_key_any(logit(c)); }, NP, K,
         k, u, S, renorm, [&](int j, int id, float w) {
 #pragma unroll
             for (int q = 0; q < KMAX; ++q)
