@@ -287,7 +287,7 @@ int elb_router_route(const void* x, const void* W_router, int64_t T, int32_t d, 
     if (T == 0) return ELB_OK;
     if (!x || !W_router || !k || !ids || !w)
         return fail(ELB_ERR_INVALID_ARG, "NULL tensor pointer");
-    if (router_route_dma_usable(dtype, T, d, N, params->K))
+    if (router_route_dma_usable(dtype, T, d, N, params->K) && aligned16(x, W_router))
         return hip_status(launch_router_route_dma(x, W_router, T, d, N, *params, logits_out, k,
                                                   ids, w, nullptr, 0, (hipStream_t)stream),
                           "router_route");
@@ -378,7 +378,8 @@ static int experts_impl(const void* x, const void* W_gate_up, const void* W_down
     int* inv = (int*)(ws + L.inv);
     void* H = ws + L.H;
     void* Y = ws + L.Y;
-    const int tr = gemm_tile_rows(dtype, T, K, N, d, m);
+    const int tr = gemm_tile_rows(dtype, T, K, N, d, m,
+                                  aligned16(x, W_gate_up) && aligned16(W_down, nullptr));
     const int64_t mt = max_tiles(T, K, N, tr);
     int* tail_list = tile_off + N + 1;
     // the large-tile kernel (256-row tiles, m / 128 tiles across per M-tile, one block per
@@ -484,10 +485,11 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
     // Router and routing, by size (the same bits on every path): up to kRouteDmaMaxT tokens one
     // launch of 16-token blocks, which also writes the dispatch histogram; larger batches with
     // N = 64 and d % 256 == 0 split the contraction over four blocks per 64 tokens (two
-    // launches, histogram included); the rest the fused one-block kernel, or the router and
-    // routing kernels for fp32 and caps above 16.
+    // launches, histogram included); the rest, and rows off a 16-byte boundary, the fused
+    // one-block kernel, or the router and routing kernels for fp32 and caps above 16.
     const bool skinny = gemm_use_skinny(dtype, T, K, N, d, m);
-    if (router_route_dma_usable(dtype, T, d, N, K)) {
+    const bool aligned = aligned16(x, W_router);
+    if (aligned && router_route_dma_usable(dtype, T, d, N, K)) {
         if (int rc = hip_status(
                 launch_router_route_dma(x, W_router, T, d, N, *params, logits_out, k, ids, w,
                                         (int*)(ws + L.hist), dispatch_hist_ld(T), s),
@@ -496,7 +498,7 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
         return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                             dtype, y, ws, L, counts_out, s, true, split_hist_subs(T));
     }
-    if (router_split_usable(dtype, T, d, N, K) && !skinny) {
+    if (aligned && router_split_usable(dtype, T, d, N, K) && !skinny) {
         if (int rc = hip_status(
                 launch_router_split_route(x, W_router, T, d, *params, (float*)(ws + L.part),
                                           logits_out, k, ids, w, (int*)(ws + L.hist),

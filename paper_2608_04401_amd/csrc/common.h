@@ -32,6 +32,19 @@ constexpr int kWave = 64;
 // LDS pointers as 32-bit LDS addresses (for the M0 operand of global_load_lds_dwordx4)
 typedef __attribute__((address_space(3))) void lds_void_t;
 
+// Tensors start on any element boundary (a view into a larger buffer), but
+// global_load_lds_dwordx4 is only relied on for 16-byte aligned sources.  Each kernel that
+// copies with it has a form with ordinary loads (DMA = false), or leaves such tensors to one
+// that loads ordinarily; the launchers ask this of every tensor a kernel copies from.
+inline bool aligned16(const void* a, const void* b) {
+    return ((uintptr_t)a | (uintptr_t)b) % 16 == 0;
+}
+typedef uint32_t u32x4_any_t __attribute__((ext_vector_type(4), aligned(2)));
+// 16 bytes from global memory at any element boundary into LDS, by an ordinary load
+__device__ __forceinline__ void copy16_any(char* lds, const char* src) {
+    *reinterpret_cast<u32x4_t*>(lds) = *reinterpret_cast<const u32x4_any_t*>(src);
+}
+
 // s_waitcnt vmcnt(n) (expcnt and lgkmcnt not waited on); n a compile-time constant
 #define ELB_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
 
@@ -126,8 +139,9 @@ hipError_t launch_router_split_route(const void* x, const void* Wr, int64_t T, i
                                      hipStream_t s);
 
 // grouped GEMMs
-// rows per M-tile of the grouped GEMMs for this problem (the dispatch scan uses the same)
-int gemm_tile_rows(int dtype, int64_t T, int K, int N, int d, int m);
+// rows per M-tile of the grouped GEMMs for this problem (the dispatch scan uses the same);
+// aligned: x and both weight tensors are 16-byte aligned
+int gemm_tile_rows(int dtype, int64_t T, int K, int N, int d, int m, bool aligned);
 // tail_list (large-tile kernels only, TilePlan): its experts' remainder rows are computed
 // by extra blocks of the same launch.  nt_weights (large-tile kernels): the weight copies carry
 // the non-temporal hint (gemm_stream_weights)

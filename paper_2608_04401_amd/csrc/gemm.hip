@@ -124,8 +124,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 // MODE 0 = gate_up (+SwiGLU -> H), 1 = down (-> Y); TM x TN: the block tile, rows (token rows of
 // the expert) x weight rows, WM: waves along the rows; rot: first k-tile of the block, < nk; nt:
-// the weight copies carry the non-temporal hint
-template <int MODE, int TM, int TN, int WM>
+// the weight copies carry the non-temporal hint; DMA: x and the weights are 16-byte aligned
+template <int MODE, int TM, int TN, int WM, bool DMA = true>
 __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
                                               const int* __restrict__ row_token,
                                               const bf16_t* __restrict__ B, int e, int row0,
@@ -191,6 +191,10 @@ __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
         for (int i = 0; i < IA; ++i) {
             const uint32_t la = lds_a + unit * AU + i * 1024;
             const char* const va = a_src[i] + kb;
+            if constexpr (!DMA) {
+                copy16_any(sma + unit * AU + (wid * IA + i) * 1024 + lane * 16, va);
+                continue;
+            }
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
                          :: "s"(la), "v"(va) : "memory", "m0");
         }
@@ -201,6 +205,10 @@ __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
         for (int i = 0; i < IB; ++i) {
             const uint32_t la = lds_b + unit * BU + i * 1024;
             const char* const va = b_src[i] + kb;
+            if constexpr (!DMA) {
+                copy16_any(smb + unit * BU + (wid * IB + i) * 1024 + lane * 16, va);
+                continue;
+            }
             if (nt)
                 asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt"
                              :: "s"(la), "v"(va) : "memory", "m0");
@@ -318,7 +326,7 @@ __device__ __forceinline__ void gemm_mid_body(const bf16_t* __restrict__ A,
     }
 }
 
-template <int MODE>
+template <int MODE, bool DMA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_mid(
     const bf16_t* __restrict__ A, const int* __restrict__ row_token,
     const bf16_t* __restrict__ B, const int* __restrict__ offsets,
@@ -335,11 +343,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int left = end - row0;
     const int rot = (int)((int64_t)ntile * (((MODE == 0) ? d : m) / 64) / nt_count);
     if (left <= 64)
-        gemm_mid_body<MODE, 64, BN, 2>(A, row_token, B, e, row0, left, ntile, rot, d, m, C, sm,
-                                       tiles == 1);
+        gemm_mid_body<MODE, 64, BN, 2, DMA>(A, row_token, B, e, row0, left, ntile, rot, d, m, C,
+                                            sm, tiles == 1);
     else
-        gemm_mid_body<MODE, 128, BN, 2>(A, row_token, B, e, row0, left < BM ? left : BM, ntile,
-                                        rot, d, m, C, sm, tiles == 1);
+        gemm_mid_body<MODE, 128, BN, 2, DMA>(A, row_token, B, e, row0, left < BM ? left : BM,
+                                             ntile, rot, d, m, C, sm, tiles == 1);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -782,7 +790,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // ------------------------------------------------------------------------------------------
 constexpr int FBM = 64, FBN = 64, FBK = 32;
 
-template <int MODE>
+template <int MODE, bool DMA>
 __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
                                                 const int* __restrict__ row_token,
                                                 const float* __restrict__ B,
@@ -834,6 +842,12 @@ __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
             const int64_t o = (int64_t)t * (FBK * 4) + (chunk[i] & mask);
             const char* const va = a_src[i] + o;
             const char* const vb = b_src[i] + o;
+            if constexpr (!DMA) {
+                char* const at = sm + unit * UNIT + wid * 2048 + i * 1024 + lane * 16;
+                copy16_any(at, va);
+                copy16_any(at + NU * UNIT, vb);
+                continue;
+            }
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
                          :: "s"(la), "v"(va) : "memory", "m0");
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
@@ -914,7 +928,7 @@ unsigned grid8(int64_t blocks) { return (unsigned)((blocks + 7) / 8 * 8); }
 
 }  // namespace
 
-int gemm_tile_rows(int dtype, int64_t T, int K, int N, int d, int m) {
+int gemm_tile_rows(int dtype, int64_t T, int K, int N, int d, int m, bool aligned) {
     if (dtype != ELB_BF16) return FBM;
     const int64_t avg_rows = T * K / (N > 0 ? N : 1);
     // the large-tile kernel's 32-bit byte offsets: gathered x rows from x itself (T d
@@ -932,7 +946,7 @@ int gemm_tile_rows(int dtype, int64_t T, int K, int N, int d, int m) {
     // needs more than 128 blocks, half of the compute units.
     const int64_t blocks = (T * K + (int64_t)N * 128) / 256 * (m / 128);
     return (m % 128 == 0 && d >= 128 && T > 0 && avg_rows >= 112 && blocks > 128 &&
-            offsets_fit) ? LBM : BM;
+            offsets_fit && aligned) ? LBM : BM;
 }
 
 hipError_t launch_gemm_gate_up(const void* x, const void* Wgu, const int* row_token,
@@ -949,13 +963,14 @@ hipError_t launch_gemm_gate_up(const void* x, const void* Wgu, const int* row_to
                            tail_list, (int)big, N, d, m, (bf16_t*)H, (int)nt_weights);
     } else if (dtype == ELB_BF16) {
         ProfileScope prof("gemm_gate_up_bf16_s", s);
-        ELB_LAUNCH(gemm_bf16_mid<0>, dim3(grid8(max_tiles * (m / 64))), dim3(256),
-                           0, s, (const bf16_t*)x, row_token, (const bf16_t*)Wgu, offsets,
-                           tile_off, N, d, m, (bf16_t*)H);
+        ELB_LAUNCH((aligned16(x, Wgu) ? gemm_bf16_mid<0, true> : gemm_bf16_mid<0, false>),
+                   dim3(grid8(max_tiles * (m / 64))), dim3(256), 0, s, (const bf16_t*)x,
+                   row_token, (const bf16_t*)Wgu, offsets, tile_off, N, d, m, (bf16_t*)H);
     } else {
         ProfileScope prof("gemm_gate_up_f32", s);
-        ELB_LAUNCH(gemm_f32<0>, dim3(grid8(max_tiles * ((m + 31) / 32))), dim3(256), 0, s, (const float*)x, row_token, (const float*)Wgu,
-                           offsets, tile_off, N, d, m, (float*)H);
+        ELB_LAUNCH((aligned16(x, Wgu) ? gemm_f32<0, true> : gemm_f32<0, false>),
+                   dim3(grid8(max_tiles * ((m + 31) / 32))), dim3(256), 0, s, (const float*)x,
+                   row_token, (const float*)Wgu, offsets, tile_off, N, d, m, (float*)H);
     }
     return hipGetLastError();
 }
@@ -974,13 +989,16 @@ hipError_t launch_gemm_down(const void* H, const void* Wd, const int* offsets,
                            tile_off, tail_list, (int)big, N, d, m, (bf16_t*)Y, (int)nt_weights);
     } else if (dtype == ELB_BF16) {
         ProfileScope prof("gemm_down_bf16_s", s);
-        ELB_LAUNCH(gemm_bf16_mid<1>, dim3(grid8(max_tiles * ((d + BN - 1) / BN))),
-                           dim3(256), 0, s, (const bf16_t*)H, (const int*)nullptr,
-                           (const bf16_t*)Wd, offsets, tile_off, N, d, m, (bf16_t*)Y);
+        ELB_LAUNCH((aligned16(H, Wd) ? gemm_bf16_mid<1, true> : gemm_bf16_mid<1, false>),
+                   dim3(grid8(max_tiles * ((d + BN - 1) / BN))), dim3(256), 0, s,
+                   (const bf16_t*)H, (const int*)nullptr, (const bf16_t*)Wd, offsets, tile_off,
+                   N, d, m, (bf16_t*)Y);
     } else {
         ProfileScope prof("gemm_down_f32", s);
-        ELB_LAUNCH(gemm_f32<1>, dim3(grid8(max_tiles * ((d + FBN - 1) / FBN))), dim3(256), 0, s, (const float*)H, (const int*)nullptr,
-                           (const float*)Wd, offsets, tile_off, N, d, m, (float*)Y);
+        ELB_LAUNCH((aligned16(H, Wd) ? gemm_f32<1, true> : gemm_f32<1, false>),
+                   dim3(grid8(max_tiles * ((d + FBN - 1) / FBN))), dim3(256), 0, s,
+                   (const float*)H, (const int*)nullptr, (const float*)Wd, offsets, tile_off, N,
+                   d, m, (float*)Y);
     }
     return hipGetLastError();
 }

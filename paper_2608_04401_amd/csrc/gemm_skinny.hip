@@ -94,7 +94,7 @@ __device__ __forceinline__ int gather_slots(const int* __restrict__ k,
 // src[i] (i < 8): the task's weight rows 8 i .. 8 i + 7 at stage 0, off[i & 1]: the lane's byte
 // offset from it.
 // ring: this wave's stage; the block's four of them hold the partial sums afterwards.
-template <int MODE, int MT>
+template <int MODE, int MT, bool DMA>
 __device__ __forceinline__ void skinny_chunk(const char* const (&src)[8],
                                              const uint32_t (&off)[2],
                                              int s0, int s1,
@@ -120,6 +120,10 @@ __device__ __forceinline__ void skinny_chunk(const char* const (&src)[8],
         for (int i = 0; i < 8; ++i) {
             const uint32_t la = lds0 + i * 1024;
             const char* const base = src[i] + (int64_t)s * 128;
+            if constexpr (!DMA) {
+                copy16_any(ring + i * 1024 + lane * 16, base + off[i & 1]);
+                continue;
+            }
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
                          :: "s"(la), "v"(off[i & 1]), "s"(base) : "memory", "m0");
         }
@@ -228,8 +232,11 @@ __device__ __forceinline__ void skinny_chunk(const char* const (&src)[8],
 // starts 8 experts' blocks and not 64 experts' of which 56 only find that they have no row
 // (OLMoE-shaped layer, T = 1: layer 45.6 -> 33.3 us, T = 4: 93 -> 72 us; from T K = N on the
 // two numberings start as many blocks).  The counts are then taken by the first block.
-template <int MODE>
-__global__ __launch_bounds__(64 * SK_NW) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_skinny(
+// DMA: the weights are 16-byte aligned (the token rows are loaded ordinarily); the form without
+// holds a stage in registers on its way, for which two waves per SIMD leave room
+template <int MODE, bool DMA>
+__global__ __launch_bounds__(64 * SK_NW)
+    __attribute__((amdgpu_waves_per_eu(DMA ? 4 : 2, DMA ? 4 : 2))) void gemm_skinny(
     const bf16_t* __restrict__ A, const int* __restrict__ k, const int* __restrict__ ids,
     int T, int K, const bf16_t* __restrict__ W, int N, int d, int m, bf16_t* __restrict__ C,
     int* __restrict__ counts) {
@@ -284,11 +291,11 @@ __global__ __launch_bounds__(64 * SK_NW) __attribute__((amdgpu_waves_per_eu(4, 4
         const int rows = n - cb < 16 * SK_MAXMT ? n - cb : 16 * SK_MAXMT;
         if (cb) __syncthreads();  // the last chunk's partial sums have been read
         if (rows <= 16)
-            skinny_chunk<MODE, 1>(src, off, s0, s1, A, list + cb, rows, K, d, m,
-                                          out_col, C, ring, lane, w);
+            skinny_chunk<MODE, 1, DMA>(src, off, s0, s1, A, list + cb, rows, K, d, m, out_col,
+                                       C, ring, lane, w);
         else
-            skinny_chunk<MODE, 2>(src, off, s0, s1, A, list + cb, rows, K, d, m,
-                                          out_col, C, ring, lane, w);
+            skinny_chunk<MODE, 2, DMA>(src, off, s0, s1, A, list + cb, rows, K, d, m, out_col,
+                                       C, ring, lane, w);
     }
 }
 
@@ -350,15 +357,15 @@ hipError_t launch_gemm_skinny(const void* x, const void* Wgu, const void* Wd, co
     const int ne = T * K < N ? (int)(T * K) : N;  // see the kernel: tasks by slot or by expert
     {
         ProfileScope prof("gemm_gate_up_skinny", s);
-        ELB_LAUNCH(gemm_skinny<0>, dim3(blocks_for(ne * (m / 32))), dim3(64 * SK_NW), 0, s,
-                   (const bf16_t*)x, k, ids, t, K, (const bf16_t*)Wgu, N, d, m, (bf16_t*)H,
+        ELB_LAUNCH((aligned16(Wgu, nullptr) ? gemm_skinny<0, true> : gemm_skinny<0, false>),
+                   dim3(blocks_for(ne * (m / 32))), dim3(64 * SK_NW), 0, s, (const bf16_t*)x, k, ids, t, K, (const bf16_t*)Wgu, N, d, m, (bf16_t*)H,
                    counts);
     }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     {
         ProfileScope prof("gemm_down_skinny", s);
-        ELB_LAUNCH(gemm_skinny<1>, dim3(blocks_for(ne * (d / 64))), dim3(64 * SK_NW), 0, s,
-                   (const bf16_t*)H, k, ids, t, K, (const bf16_t*)Wd, N, d, m, (bf16_t*)Y,
+        ELB_LAUNCH((aligned16(Wd, nullptr) ? gemm_skinny<1, true> : gemm_skinny<1, false>),
+                   dim3(blocks_for(ne * (d / 64))), dim3(64 * SK_NW), 0, s, (const bf16_t*)H, k, ids, t, K, (const bf16_t*)Wd, N, d, m, (bf16_t*)Y,
                    (int*)nullptr);
     }
     return hipGetLastError();
