@@ -21,6 +21,7 @@
 //  - decode-sized batches use gemm_skinny.hip instead (weight streaming).
 // fp32 path: gemm_f32, 64 x 64 x 32 tiles on the fp32 matrix instructions.
 #include "gemm_stream.h"
+#include "tilegrid.h"
 
 namespace elb {
 
@@ -801,7 +802,8 @@ __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
     __shared__ __attribute__((aligned(1024))) char sm[2 * NU * UNIT];
     const int nt_count = (MODE == 0) ? (m + 31) / 32 : (d + FBN - 1) / FBN;
     int tile, ntile;
-    if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
+    const int block = blockIdx.y * kTileGridRow + blockIdx.x;
+    if (!xcd_tile(block, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
     int e, row0, rows;
     bool alone;
     find_tile(tile_off, offsets, N, tile, FBM, e, row0, rows, alone);
@@ -925,6 +927,12 @@ __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
 }
 
 unsigned grid8(int64_t blocks) { return (unsigned)((blocks + 7) / 8 * 8); }
+// the fp32 kernel's grid: its blocks write 8 KB of H, so 137 GB of it are 2^24 blocks (the bf16
+// kernels' blocks write 16 KB or more, and theirs fit one dimension)
+dim3 grid_f32(int64_t blocks) {
+    const TileGrid g = tile_grid(blocks);
+    return dim3(g.x, g.y);
+}
 
 }  // namespace
 
@@ -969,7 +977,7 @@ hipError_t launch_gemm_gate_up(const void* x, const void* Wgu, const int* row_to
     } else {
         ProfileScope prof("gemm_gate_up_f32", s);
         ELB_LAUNCH((aligned16(x, Wgu) ? gemm_f32<0, true> : gemm_f32<0, false>),
-                   dim3(grid8(max_tiles * ((m + 31) / 32))), dim3(256), 0, s, (const float*)x,
+                   grid_f32(max_tiles * ((m + 31) / 32)), dim3(256), 0, s, (const float*)x,
                    row_token, (const float*)Wgu, offsets, tile_off, N, d, m, (float*)H);
     }
     return hipGetLastError();
@@ -996,7 +1004,7 @@ hipError_t launch_gemm_down(const void* H, const void* Wd, const int* offsets,
     } else {
         ProfileScope prof("gemm_down_f32", s);
         ELB_LAUNCH((aligned16(H, Wd) ? gemm_f32<1, true> : gemm_f32<1, false>),
-                   dim3(grid8(max_tiles * ((d + FBN - 1) / FBN))), dim3(256), 0, s,
+                   grid_f32(max_tiles * ((d + FBN - 1) / FBN)), dim3(256), 0, s,
                    (const float*)H, (const int*)nullptr, (const float*)Wd, offsets, tile_off, N,
                    d, m, (float*)Y);
     }
