@@ -1,4 +1,4 @@
-"""GPU parity of the expert stage at sizes whose byte offsets pass 2^32.
+"""GPU parity of the expert stage at sizes whose byte offsets or launches pass 2^32.
 
 The large-tile grouped GEMM adds a 32-bit per-lane byte offset to a 64-bit base.  These tests
 run problems where a flat offset from the start of a tensor would wrap:
@@ -77,4 +77,17 @@ def test_gate_up_gathered_x_past_4gib():
                                          rng.choice(T, 128, replace=False)]))
     tok, rel = _run(T, d, N, m, 21, pick)
     print("x past 4 GiB: %d tokens, max rel %.3e" % (len(tok), rel.max()))
+    assert rel.max() < RTOL_BF16
+
+
+def test_more_than_2_24_tokens():
+    """T = 2^24 + 1000 tokens, d = 64, m = 64, N = 4, K = 1: as many combine blocks as a launch
+    dimension of 2^32 threads cannot hold; the last tokens and a sample are checked."""
+    T, d, N, m = (1 << 24) + 1000, 64, 4, 64
+    rng = np.random.default_rng(2)
+
+    def pick(ids_h):
+        return np.unique(np.concatenate([np.arange(T - 1000, T), rng.choice(T, 1000)]))
+    tok, rel = _run(T, d, N, m, 31, pick)
+    print("2^24 tokens: %d tokens, max rel %.3e" % (len(tok), rel.max()))
     assert rel.max() < RTOL_BF16
