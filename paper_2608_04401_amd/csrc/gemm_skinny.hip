@@ -29,9 +29,16 @@
 // weights per chunk (rare where this path is chosen: at most 16 rows per expert on
 // average).
 //
-// Block -> task mapping: blocks are numbered expert-major and each of the 8 XCDs (block b
+// Block -> task mapping: tasks are numbered expert-major and each of the 8 XCDs (block b
 // runs on XCD b % 8) takes a contiguous range of them, so an expert's token rows are shared
-// through one XCD's L2.
+// through one XCD's L2.  With at most two slots per expert many experts have no token, and an
+// XCD whose range holds few used ones is done early while another streams all of its own; then
+// (`spread`) consecutive tasks go to consecutive XCDs, so that every XCD streams an eighth of
+// each used expert.  OLMoE-shaped layer, us, ranges / spread: 8 tokens 109 / 94, 9 113 / 101, 10
+// 114 / 108, 16 126 / 125; from there on the ranges are faster (20 tokens 128 / 129, 64 133 / 139).
+// Small layers, whose time is not the stream's, lose by it (d = 2048, N = 8, m = 576: 29.8 / 30.5;
+// d = 1024, N = 64, m = 768, 302 MB of weights: 54.2 / 54.7), so it takes twice the last-level
+// cache of weights.
 //
 // Measured (OLMoE-shaped layer, T = 64, gate/up + down): 126 + 54 us with one wave per 64-row
 // task loading operands straight into registers, 79 + 42 us (6.8 and 6.4 TB/s of weights, the
@@ -232,14 +239,15 @@ __device__ __forceinline__ void skinny_chunk(const char* const (&src)[8],
 // starts 8 experts' blocks and not 64 experts' of which 56 only find that they have no row
 // (OLMoE-shaped layer, T = 1: layer 45.6 -> 33.3 us, T = 4: 93 -> 72 us; from T K = N on the
 // two numberings start as many blocks).  The counts are then taken by the first block.
+// spread: see above.
 // DMA: the weights are 16-byte aligned (the token rows are loaded ordinarily); the form without
 // holds a stage in registers on its way, for which two waves per SIMD leave room
 template <int MODE, bool DMA>
 __global__ __launch_bounds__(64 * SK_NW)
     __attribute__((amdgpu_waves_per_eu(DMA ? 4 : 2, DMA ? 4 : 2))) void gemm_skinny(
     const bf16_t* __restrict__ A, const int* __restrict__ k, const int* __restrict__ ids,
-    int T, int K, const bf16_t* __restrict__ W, int N, int d, int m, bf16_t* __restrict__ C,
-    int* __restrict__ counts) {
+    int T, int K, const bf16_t* __restrict__ W, int N, int d, int m, int spread,
+    bf16_t* __restrict__ C, int* __restrict__ counts) {
     __shared__ __attribute__((aligned(1024))) char ring[SK_NW * SK_STAGE];
     __shared__ int list[kSlotMax];
     __shared__ int wave_n[SK_NW];
@@ -250,7 +258,7 @@ __global__ __launch_bounds__(64 * SK_NW)
     const int tasks = (by_slot ? T * K : N) * per_e;
     const int per = (tasks + 7) >> 3;
     const int s = blockIdx.x >> 3;
-    const int task = (blockIdx.x & 7) * per + s;
+    const int task = spread ? (int)blockIdx.x : (int)(blockIdx.x & 7) * per + s;
     if (s >= per || task >= tasks) return;  // block-uniform
     const int i_e = task / per_e, c = task - i_e * per_e;
     int e = i_e;
@@ -355,18 +363,20 @@ hipError_t launch_gemm_skinny(const void* x, const void* Wgu, const void* Wd, co
                               void* Y, int* counts, hipStream_t s) {
     const int t = (int)T;
     const int ne = T * K < N ? (int)(T * K) : N;  // see the kernel: tasks by slot or by expert
+    const int spread = T * K <= 2 * N &&
+                       (double)N * d * m * 6 > 2.0 * (double)kLastLevelCacheBytes;
     {
         ProfileScope prof("gemm_gate_up_skinny", s);
         ELB_LAUNCH((aligned16(Wgu, nullptr) ? gemm_skinny<0, true> : gemm_skinny<0, false>),
-                   dim3(blocks_for(ne * (m / 32))), dim3(64 * SK_NW), 0, s, (const bf16_t*)x, k, ids, t, K, (const bf16_t*)Wgu, N, d, m, (bf16_t*)H,
-                   counts);
+                   dim3(blocks_for(ne * (m / 32))), dim3(64 * SK_NW), 0, s, (const bf16_t*)x, k,
+                   ids, t, K, (const bf16_t*)Wgu, N, d, m, spread, (bf16_t*)H, counts);
     }
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     {
         ProfileScope prof("gemm_down_skinny", s);
         ELB_LAUNCH((aligned16(Wd, nullptr) ? gemm_skinny<1, true> : gemm_skinny<1, false>),
-                   dim3(blocks_for(ne * (d / 64))), dim3(64 * SK_NW), 0, s, (const bf16_t*)H, k, ids, t, K, (const bf16_t*)Wd, N, d, m, (bf16_t*)Y,
-                   (int*)nullptr);
+                   dim3(blocks_for(ne * (d / 64))), dim3(64 * SK_NW), 0, s, (const bf16_t*)H, k,
+                   ids, t, K, (const bf16_t*)Wd, N, d, m, spread, (bf16_t*)Y, (int*)nullptr);
     }
     return hipGetLastError();
 }

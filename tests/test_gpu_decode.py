@@ -135,3 +135,19 @@ def test_decode_one_expert_for_all_tokens(T):
     k[T // 2] = 1  # its second slot is not used, whatever its id
     w = np.tile(np.array([[0.6, 0.3, 0.0]], np.float32), (T, 1))
     assert _experts(L, k, ids, w).max() < RTOL_BF16
+
+
+@pytest.mark.parametrize("T", [2, 8, 9, 16, 17])
+def test_decode_tasks_spread_over_xcds(T):
+    """OLMoE-shaped weights (more than twice the last-level cache) with T K on both sides of N
+    and of 2 N: tasks dealt out to the XCDs in turn up to 2 N slots, in ranges above; outputs and
+    counts."""
+    L = synth.olmoe_layer(T=T, seed=80 + T)
+    x, Wr, Wgu, Wd = _gpu(L)
+    y, dbg = B.elb_moe_forward(x, Wr, Wgu, Wd, K=8, mode=B.MODE_TOPK, debug=True)
+    torch.cuda.synchronize()
+    ids = cpu(dbg["ids"])
+    assert (cpu(dbg["counts"]) == np.bincount(ids.ravel(), minlength=64)).all()
+    ref = O.moe_experts(L.x, L.W_gu, L.W_down, cpu(dbg["k"]), ids,
+                        cpu(dbg["w"]).astype(np.float64))
+    assert rel_err_rows(cpu(y), ref).max() < RTOL_BF16
