@@ -159,6 +159,32 @@ def test_layer_one_launch_router_any_shape(T, d, N, K, mode, eps, renorm):
     assert torch.equal(y, y2)
 
 
+@pytest.mark.parametrize("T,d,N,K", [(4097, 64, 5, 5), (4100, 96, 8, 8), (4111, 320, 16, 16),
+                                     (4200, 128, 17, 8), (5000, 448, 32, 9), (4113, 64, 48, 16),
+                                     (8200, 192, 60, 8), (8209, 64, 33, 12), (4112, 320, 64, 8),
+                                     (8250, 96, 64, 16), (4097, 64, 2, 1), (4101, 128, 32, 8),
+                                     (4099, 192, 8, 4), (4098, 128, 16, 8)])
+@pytest.mark.parametrize("mode,eps,renorm", [(B.MODE_ELBOW, 0.0, True), (B.MODE_TOPK, 1e-8, False)])
+def test_one_kernel_router_above_4096_tokens(T, d, N, K, mode, eps, renorm):
+    """Above 4096 tokens, with N < 64 or d % 256 != 0, router_route_bf16 (its one-lane forms for
+    8, 16, 32 and 64 experts, full and not, both caps; N = 64: 16 lanes) in elb_router_route and
+    in the layer, whose dispatch counts the assignments itself: the two-step path's bits, the
+    counts of the routing, and the expert stage's bits on it."""
+    L, k, ids, w = _case(T, d, N, K, seed=T + d + N, mode=mode, eps=eps, renormalize=renorm)
+    if d % 64:
+        return  # the expert stage needs it
+    x, Wr, Wgu, Wd = (to_gpu(a, BF) for a in (L.x, L.W_router, L.W_gu, L.W_down))
+    y, dbg = B.elb_moe_forward(x, Wr, Wgu, Wd, K=K, eps=eps, mode=mode, renormalize=renorm,
+                               debug=True)
+    torch.cuda.synchronize()
+    assert torch.equal(dbg["k"], k) and torch.equal(dbg["ids"], ids) and torch.equal(dbg["w"], w)
+    ii = cpu(ids)
+    assert np.array_equal(cpu(dbg["counts"]), np.bincount(ii[ii >= 0], minlength=N))
+    y2 = B.elb_moe_experts(x, Wgu, Wd, k, ids, w)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y2)
+
+
 @pytest.mark.parametrize("N,K", [(5, 3), (24, 8), (60, 8)])
 def test_one_launch_router_ties(N, K):
     """Equal logits (identical W_r rows in pairs, and a zero token whose logits are all equal):

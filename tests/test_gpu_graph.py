@@ -5,11 +5,10 @@ bit.  Between replays the static input is overwritten in place and eager layer c
 other inputs run on the same stream (on their own workspace: the graph's lies in its memory
 pool), and each replay is checked against a fresh eager call on the new input.
 
-Cases cover each path the forward takes by size: the OLMoE-shaped prefill layer (split
+Cases cover each path the forward takes by size: the OLMoE-shaped prefill layer (one-launch
 router, histogram-fed dispatch, large-tile GEMMs with remainder blocks), the decode-sized
-layer (small-batch router, weight-streaming GEMMs, packed weights too), a mid-sized layer
-with other expert counts (fused router + routing, count/scatter dispatch, 128-row GEMMs) and
-the allocation-free entry point."""
+layer (weight-streaming GEMMs; the packed entry point too), a mid-sized layer with other
+expert counts (128-row GEMMs) and the allocation-free entry point."""
 import pytest
 import torch
 
