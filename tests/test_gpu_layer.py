@@ -33,7 +33,8 @@ def olmoe():
                                    (200, 64, 64), (130, 17, 5), (255, 3, 3), (8192, 64, 8),
                                    (8193, 64, 8), (5000, 64, 64), (8000, 7, 2)])
 def test_dispatch_matches_oracle(T, N, K):
-    """T <= 256 runs the single-block dispatch, larger T the three-launch one."""
+    """T <= 256 runs the single-block dispatch, larger T count and scatter, from T = 8193 on with
+    a scan launch between them."""
     lg = synth.planted_logits(T, N, seed=T + N, m_max=min(8, N))
     r = O.route(lg, K=K)
     counts, offsets, row_token, inv = B.elb_dispatch(to_gpu(r.k, torch.int32),
@@ -133,11 +134,17 @@ def test_experts_bf16_ragged_with_residual():
     _experts_case(L, BF, 4, O.MODE_ELBOW, RTOL_BF16, residual=res)
 
 
-@pytest.mark.parametrize("T,d,N,m,K", [(1000, 192, 8, 128, 2), (1536, 320, 4, 256, 2)])
-def test_experts_bf16_large_tiles_ragged(T, d, N, m, K):
-    """Shapes on the 256-row tile path (>= 192 rows per expert on average) with a partial
-    output tile in the down GEMM (d not a multiple of 256) and few k-tiles (d = 192: 3 in
-    the gate/up GEMM; m = 128: 2 in the down GEMM), with a residual."""
+@pytest.mark.parametrize("T,d,N,m,K,large", [(1000, 192, 8, 128, 2, False),
+                                             (1536, 320, 4, 256, 2, False),
+                                             (16100, 192, 8, 128, 2, True),
+                                             (8200, 320, 4, 256, 2, True)])
+def test_experts_bf16_large_tiles_ragged(T, d, N, m, K, large):
+    """Many rows per expert (>= 192 on average) with a partial output tile in the down GEMM (d
+    not a multiple of 256) and few k-tiles (d = 192: 3 in the gate/up GEMM; m = 128: 2 in the
+    down GEMM), with a residual: on the 256-row kernel where it has more than 128 blocks
+    (large), else on the 128-row one."""
+    rows = T * K
+    assert rows // N >= 112 and ((rows + 128 * N) // 256 * (m // 128) > 128) == large
     L = synth.moe_layer(T, d, N, m, dtype="bf16", seed=T + d)
     res = synth.round_bf16(synth.gaussian_logits(T, d, seed=7))
     _experts_case(L, BF, K, O.MODE_ELBOW, RTOL_BF16, residual=res)
@@ -231,9 +238,9 @@ def _forward_case(L, dtype, K, mode, rtol, sample=None, seed=0, label="forward",
 @pytest.mark.parametrize("T", [768, 1024])
 @pytest.mark.parametrize("mode", [O.MODE_ELBOW, O.MODE_TOPK])
 def test_forward_bf16_olmoe_mid_batches_all_tokens(olmoe, T, mode):
-    """The headline layer's weights at mid-sized batches (the first T of its tokens): 90 to
-    128 rows per expert, where the 256-row tile kernel takes over from the 128-row one (most
-    experts fill less than half of their one M-tile), on every token."""
+    """The headline layer's weights at mid-sized batches (the first T of its tokens): 96 and
+    128 rows per expert, on both sides of where the 256-row tile kernel takes over from the
+    128-row one (most experts fill less than half of their one M-tile), on every token."""
     L = olmoe[0]
     Lt = synth.LayerInputs(L.x[:T].copy(), L.W_router, L.W_gu, L.W_down, L.dtype)
     _forward_case(Lt, BF, 8, mode, RTOL_BF16, label="olmoe T=%d" % T)
@@ -258,9 +265,9 @@ def test_forward_bf16_olmoe_prefill_all_tokens(olmoe, mode):
                                              (1500, 384, 16, 128, 6, O.MODE_TOPK),
                                              (3000, 256, 40, 128, 8, O.MODE_ELBOW)])
 def test_forward_bf16_other_expert_counts_all_tokens(T, d, N, m, K, mode):
-    """Whole bf16 layers with N = 32, 16 and 40 experts (the fused router with N < 64, the
-    one-lane routing at NP = 32 / 16 / 64 with pads, the dispatch with N < 64 and the grouped
-    GEMMs at other tile fills): every token against the oracle."""
+    """Whole bf16 layers with N = 32, 16 and 40 experts (the one-launch router with N < 64, the
+    dispatch with N < 64 and the 128-row GEMMs at other tile fills): every token against the
+    oracle."""
     L = synth.moe_layer(T, d, N, m, dtype="bf16", seed=T + N)
     _forward_case(L, BF, K, mode, RTOL_BF16, label="bf16 N=%d" % N)
 
@@ -273,8 +280,8 @@ def test_forward_bf16_olmoe_prefill_renormalized_all_tokens(olmoe, mode):
 
 
 def test_forward_bf16_small_renormalized_all_tokens():
-    """Renormalised weights through the one-kernel fused router (N = 64 at T > 1024 but d not
-    a multiple of 256) and through the small-batch path (T <= 1024)."""
+    """Renormalised weights through the one-launch router, with d not a multiple of 256 (its
+    general form) and with d = 256."""
     _forward_case(synth.moe_layer(1200, 320, 64, 128, dtype="bf16", seed=7), BF, 8,
                   O.MODE_ELBOW, RTOL_BF16, label="fused renorm", renorm=True)
     _forward_case(synth.moe_layer(300, 256, 64, 128, dtype="bf16", seed=8), BF, 8,
@@ -284,8 +291,8 @@ def test_forward_bf16_small_renormalized_all_tokens():
 @pytest.mark.parametrize("K", [1, 2])
 def test_forward_bf16_small_caps_all_tokens(K):
     """Caps K = 1 (the layer is argmax routing: k = 1 for every token) and K = 2 on an
-    OLMoE-width layer at T = 2048 (the split router; few rows per expert, so the 128-row GEMM
-    tiles): every token against the oracle."""
+    OLMoE-width layer at T = 2048 (few rows per expert, so the 128-row GEMM tiles): every token
+    against the oracle."""
     L = synth.moe_layer(2048, 2048, 64, 256, dtype="bf16", seed=30 + K)
     y, dbg = _forward_case(L, BF, K, O.MODE_ELBOW, RTOL_BF16, label="K=%d" % K)
     if K == 1:
