@@ -322,9 +322,9 @@ def routing_variants(B, torch, T=65536, N=64, K=8, nbuf=16, iters=48):
 
 def decode_layer(B, torch, synth, K=8, steps=100):
     """The OLMoE-shaped layer at a decode batch (T = 64): latency per layer call, elbow and
-    top-8, with the expert weights in their packed copy (elb_pack_expert_weights, made once
-    before timing) and, for comparison, row-major; and the weight stream of the expert GEMMs
-    against HBM bandwidth (packed)."""
+    top-8, through the entry point that takes a packed weight copy and (elbow, "row_major")
+    through the one that does not; the kernels read the row-major weights in both.  And the
+    weight stream of the expert GEMMs against HBM bandwidth."""
     T, d, N, m = WORKLOADS["olmoe-decode"][:4]
     L = synth.moe_layer(T, d, N, m, dtype="bf16", seed=0)
     gpu = tuple(torch.from_numpy(a).to("cuda").to(torch.bfloat16)
@@ -337,8 +337,8 @@ def decode_layer(B, torch, synth, K=8, steps=100):
             "k": dbg["k"].cpu().numpy(), "ids": dbg["ids"].cpu().numpy(),
             "w": dbg["w"].cpu().numpy()}
     sum_k, used = int(counts.sum()), int((counts > 0).sum())
-    out = {"workload": "olmoe-decode: T=%d d_model=%d N=%d m=%d K=%d bf16, packed expert "
-                       "weights" % (T, d, N, m, K),
+    out = {"workload": "olmoe-decode: T=%d d_model=%d N=%d m=%d K=%d bf16, packed copy "
+                       "passed (not read)" % (T, d, N, m, K),
            "experts_used": used, "mean_k": round(sum_k / T, 4)}
     for name, mode in (("elbow", B.MODE_ELBOW), ("topk", B.MODE_TOPK)):
         ms, _ = time_layer(B, torch, gpu, K, mode, steps, 10, False, packed)

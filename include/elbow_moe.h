@@ -250,10 +250,10 @@ int elb_moe_forward_noalloc(const void *x, const void *W_router, const void *W_g
  *   W_gate_up [N, 2m, d], W_down [N, d, m]   bf16 input (as for elb_moe_experts)
  *   packed                                   device output, elb_packed_expert_bytes bytes
  * elb_moe_experts_packed / elb_moe_forward_packed are elb_moe_experts / elb_moe_forward with
- * that copy (or NULL) as an extra argument.  The decode-sized kernels now stream the row-major
- * weights at the rate they once needed the copy for, so every path reads W_gate_up and W_down
- * (both are required, as before) and the copy is not read: results are bit-identical to the
- * unpacked calls, and a program can save the copy's memory.
+ * that copy (or NULL) as an extra argument, kept for compatibility: the decode-sized kernels
+ * stream the row-major weights at the rate they once needed the copy for, so every path reads
+ * W_gate_up and W_down (both are required, as before) and the copy is not read.  Results are
+ * bit-identical to the unpacked calls, and a program can save the copy's memory.
  */
 size_t elb_packed_expert_bytes(int32_t N, int32_t d, int32_t m);
 int elb_pack_expert_weights(const void *W_gate_up, const void *W_down, int32_t N, int32_t d,

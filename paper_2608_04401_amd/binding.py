@@ -260,7 +260,8 @@ def elb_moe_workspace_bytes(T: int, d: int, N: int, m: int, K: int, dtype: int) 
 
 
 def elb_pack_expert_weights(W_gate_up: torch.Tensor, W_down: torch.Tensor) -> torch.Tensor:
-    """The packed copy of bf16 expert weights for the decode-sized path (uint8 tensor)."""
+    """The packed copy of bf16 expert weights (uint8 tensor), in the order the header gives.  No
+    kernel of the library reads it any more: a program needs it only for code of its own."""
     _dev(W_gate_up, W_down)
     N, m2, d = W_gate_up.shape
     m = m2 // 2
@@ -274,7 +275,8 @@ def elb_pack_expert_weights(W_gate_up: torch.Tensor, W_down: torch.Tensor) -> to
 
 def elb_moe_experts(x, W_gate_up, W_down, k, ids, w, residual=None, out=None,
                     packed=None) -> torch.Tensor:
-    """packed: optional packed weights (elb_pack_expert_weights) for the decode-sized path."""
+    """packed: optional packed weights (elb_pack_expert_weights), kept for compatibility: not
+    read, the same bits without."""
     _dev(x, W_gate_up, W_down, k, ids, w, residual, out, packed)
     T, d = x.shape
     N, m2, _ = W_gate_up.shape
@@ -300,7 +302,8 @@ def elb_moe_forward(x, W_router, W_gate_up, W_down, K: int = 8, eps: float = 1e-
                     mode: int = MODE_ELBOW, renormalize: bool = False, residual=None,
                     out=None, debug: bool = False, packed=None):
     """The whole layer.  Returns y, or (y, dict of intermediates) when debug=True.
-    packed: optional packed weights (elb_pack_expert_weights) for the decode-sized path."""
+    packed: optional packed weights (elb_pack_expert_weights), kept for compatibility: not read,
+    the same bits without."""
     _dev(x, W_router, W_gate_up, W_down, residual, out, packed)
     T, d = x.shape
     N = W_router.shape[0]

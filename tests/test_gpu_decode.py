@@ -78,8 +78,8 @@ def test_experts_decode_shapes(T, d, N, m, K):
 
 @pytest.mark.parametrize("T", [1, 64, 128])
 def test_forward_decode_packed_weights_bit_identical(T):
-    """The packed copy of the weights gives the same bits as the row-major weights (same
-    operands, same accumulation order), and parity with the oracle."""
+    """The entry point that takes a packed copy gives the bits of the one that does not (neither
+    reads the copy; its contents are checked below), and parity with the oracle."""
     L = synth.olmoe_layer(T=T, seed=50 + T)
     x, Wr, Wgu, Wd = _gpu(L)
     packed = B.elb_pack_expert_weights(Wgu, Wd)
@@ -107,6 +107,26 @@ def test_experts_decode_packed_small_widths(T, d, N, m, K):
     y1 = B.elb_moe_experts(x, Wgu, Wd, *args, packed=packed)
     torch.cuda.synchronize()
     assert torch.equal(y0.view(torch.int16), y1.view(torch.int16))
+
+
+@pytest.mark.parametrize("d,N,m", [(64, 3, 64), (320, 2, 192), (128, 5, 256)])
+def test_packed_copy_order(d, N, m):
+    """The packed copy is the weights in the documented order: per expert and 64-row task (32
+    gate rows and the matching 32 up rows; 64 down rows), 64-deep stage, 32-deep half and 16-row
+    fragment, lane l's 8 values being row l % 16 at k = 8 (l / 16)."""
+    rng = np.random.default_rng(d)
+    Wgu, Wd = (torch.from_numpy(rng.integers(-2 ** 15, 2 ** 15, s).astype(np.int16)).cuda()
+               for s in ((N, 2 * m, d), (N, d, m)))
+    packed = B.elb_pack_expert_weights(Wgu.view(BF), Wd.view(BF)).view(torch.int16)
+    torch.cuda.synchronize()
+
+    def order(task_rows):  # [N, tasks, 64 rows, k] -> stage, half, fragment, lane / 16, row, 8
+        n, c, _, k = task_rows.shape
+        return task_rows.reshape(n, c, 4, 16, k // 64, 2, 4, 8).permute(0, 1, 4, 5, 2, 6, 3, 7)
+    gate, up = (Wgu[:, i * m:(i + 1) * m].reshape(N, m // 32, 32, d) for i in range(2))
+    want = torch.cat([order(torch.cat([gate, up], dim=2)).reshape(-1),
+                      order(Wd.reshape(N, d // 64, 64, m)).reshape(-1)])
+    assert torch.equal(packed, want)
 
 
 @pytest.mark.parametrize("T,K,N", [(1, 8, 64), (3, 4, 16), (7, 8, 64), (8, 8, 64), (9, 7, 64)])
