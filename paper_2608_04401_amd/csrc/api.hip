@@ -487,7 +487,6 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
     // N = 64 and d % 256 == 0 split the contraction over four blocks per 64 tokens (two
     // launches, histogram included); the rest, and rows off a 16-byte boundary, the fused
     // one-block kernel, or the router and routing kernels for fp32 and caps above 16.
-    const bool skinny = gemm_use_skinny(dtype, T, K, N, d, m);
     const bool aligned = aligned16(x, W_router);
     if (aligned && router_route_dma_usable(dtype, T, d, N, K)) {
         if (int rc = hip_status(
@@ -498,7 +497,7 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
         return experts_impl(x, W_gate_up, W_down, k, ids, w, residual, T, d, N, m, K,
                             dtype, y, ws, L, counts_out, s, true, split_hist_subs(T));
     }
-    if (aligned && router_split_usable(dtype, T, d, N, K) && !skinny) {
+    if (aligned && router_split_usable(dtype, T, d, N, K)) {
         if (int rc = hip_status(
                 launch_router_split_route(x, W_router, T, d, *params, (float*)(ws + L.part),
                                           logits_out, k, ids, w, (int*)(ws + L.hist),

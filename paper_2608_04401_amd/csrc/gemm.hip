@@ -59,8 +59,6 @@ __device__ __forceinline__ void find_tile(const int* __restrict__ tile_off,
     alone = tiles == 1;
 }
 
-// silu(z) = z / (1 + e^-z), with a hardware reciprocal (the result is rounded to bf16 or
-// compared at 1e-4 in fp32, far above its error)
 // Block -> tile mapping.  Blocks are dispatched round-robin over the 8 XCDs (block b runs on
 // XCD b % 8), and each XCD has its own L2.  Tiles are numbered expert-major, M-tile, then
 // N-tile innermost, and XCD x takes the contiguous range [x * per, (x + 1) * per) of that
@@ -77,6 +75,8 @@ __device__ __forceinline__ bool xcd_tile(int b, int total, int nt_count, int& mt
     return true;
 }
 
+// silu(z) = z / (1 + e^-z), with a hardware reciprocal (the result is rounded to bf16 or
+// compared at 1e-4 in fp32, far above its error)
 __device__ __forceinline__ float silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z));
 }
@@ -97,7 +97,10 @@ __device__ __forceinline__ float silu(float z) {
 //  - block (e, ntile) starts its contraction at k-tile ntile nk / nt_count and wraps around:
 //    weight rows lie a multiple of 1 KB or more apart, and blocks that all walk the same
 //    columns at the same time crowd onto part of the memory channels (gate/up at 60 rows per
-//    expert, the former register-staged form of this kernel: 135 us in step, 107 us rotated);
+//    expert, the former register-staged form of this kernel: 135 us in step, 107 us rotated).
+//    Also with many M-tiles per expert, where it matters little (layer us, rotated / experts of
+//    two tiles or more in step: 4096 tokens top-8, m = 1088, N = 64 611 / 624; d = 1024, m = 576,
+//    N = 32 147 / 148; 8192 tokens top-2, d = 1024, m = 192, N = 8 67.5 / 66.5);
 //  - the M-tiles of an expert that share a weight tile are neighbours on one XCD and start at
 //    the same k-tile, so the second one finds most of the weights in L2.  Weights that only
 //    one tile reads carry the non-temporal hint, shared ones do not (two tiles per expert, 152

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(64 * RW) void router_route_bf16(
     }
 }
 
-// ---- split router: the layer's router and routing for large batches (N = 64) ----
+// ---- split router: the layer's router and routing above kRouteDmaMaxT tokens (N = 64) ----
 //
 // router_split_bf16: block (64-token group, slice s) computes partial logit P_s of its 64
 // tokens x 64 experts over slice s of the contraction (router_slice), in the same MFMA
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256) void route_split_sum_x16(const float* __restri
     }
 }
 
-// ---- one launch for router + routing: N = 64, d % 256 == 0, T <= kRouteDmaMaxT ----
+// ---- one launch for router + routing: T <= kRouteDmaMaxT ----
 //
 // router_route_dma: block b takes tokens [16 b, 16 b + 16) (quarter b % 4 of 64-token group
 // b / 4), wave w quarter w of the contraction (router_slice), as router_split_bf16 does for
@@ -427,9 +427,9 @@ __global__ __launch_bounds__(256) void route_split_sum_x16(const float* __restri
 // loop has no barrier.  A quarter of an odd number of 32-deep steps (d % 256 != 0) ends in half
 // a chunk.  Experts are taken in groups of 16 (NG of them; rows past N repeat row N - 1), and
 // logits past N are -inf: they sort last, add exact zeros to S and never win the argmin, so
-// every N gives the bits of the one-lane routing.  The MFMA chains, the sum ((P0 + P1) + P2) + P3 and the 16-lane routing
-// (route_token_x16) are those of router_split_bf16 + route_split_sum_x16, so the logits,
-// k, ids and weights are the same bits.  hist (optional): the block's per-expert assignment
+// every N gives the bits of the one-lane routing.  The MFMA chains, the sum
+// ((P0 + P1) + P2) + P3 and the 16-lane routing (route_token_x16) are those of
+// router_split_bf16 + route_split_sum_x16, so the logits, k, ids and weights are the same bits.  hist (optional): the block's per-expert assignment
 // counts go to histogram b % 4, row b / 4, as route_split_sum_x16 writes them (the grid has
 // four blocks per 64-token group; blocks past the last token write zero counts).
 constexpr int kDmaRing = 4;                // chunks in a wave's ring
@@ -726,8 +726,8 @@ hipError_t launch_router_route_dma(const void* x, const void* Wr, int64_t T, int
 }
 
 bool router_split_usable(int dtype, int64_t T, int d, int N, int K) {
-    return dtype == ELB_BF16 && N == 64 && K <= kLaneMaxK && T > kSmallBatch && d % 256 == 0 &&
-           d <= (1 << 20);
+    return dtype == ELB_BF16 && N == 64 && K <= kLaneMaxK && T > kRouteDmaMaxT &&
+           d % 256 == 0 && d <= (1 << 20);
 }
 
 hipError_t launch_router_split_route(const void* x, const void* Wr, int64_t T, int d,
