@@ -144,7 +144,7 @@ hipError_t launch_router_split_route(const void* x, const void* Wr, int64_t T, i
 // aligned: x and both weight tensors are 16-byte aligned
 int gemm_tile_rows(int dtype, int64_t T, int K, int N, int d, int m, bool aligned);
 // tail_list (large-tile kernels only, TilePlan): its experts' remainder rows are computed
-// by extra blocks of the same launch.  nt_weights (large-tile kernels): the weight copies carry
+// by extra blocks of the same launch.  nt_weights (large-tile kernels): weight copies may carry
 // the non-temporal hint (gemm_stream_weights)
 hipError_t launch_gemm_gate_up(const void* x, const void* Wgu, const int* row_token,
                                const int* offsets, const int* tile_off, const int* tail_list,
@@ -154,9 +154,10 @@ hipError_t launch_gemm_down(const void* H, const void* Wd, const int* offsets,
                             const int* tile_off, const int* tail_list, int64_t max_tiles,
                             int tile_rows, int d, int N, int m, int dtype, void* Y,
                             hipStream_t s, bool nt_weights);
-// whether the large-tile GEMMs stream the weights with the non-temporal hint: yes while an
-// expert has at most about three M-tiles of rows (its weight tiles are read by few blocks),
-// no above, where the tiles are read by many blocks and are better kept in the caches
+// whether the large-tile GEMMs may stream weights with the non-temporal hint (of the experts
+// with few tiles that read them in step, gemm_dma_body): yes while an expert has at most about
+// three M-tiles of rows, no above, where the tiles are read by many blocks and are better kept
+// in the caches
 inline bool gemm_stream_weights(int64_t T, int K, int N) {
     return T * K < (int64_t)768 * (N > 0 ? N : 1);
 }

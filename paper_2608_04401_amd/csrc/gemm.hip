@@ -47,16 +47,17 @@ __device__ __forceinline__ void find_expert(const int* __restrict__ tile_off,
     end = __builtin_amdgcn_readlane(r1, e);
 }
 
-// M-tile `tile` (tile_rows rows): its expert e, first row, rows; alone: e has no other tile
+// M-tile `tile` (tile_rows rows): its expert e, first row, rows; tiles: e's tiles, last: the rows
+// from its last tile on
 __device__ __forceinline__ void find_tile(const int* __restrict__ tile_off,
                                           const int* __restrict__ offsets, int N, int tile,
                                           int tile_rows, int& e, int& row0, int& rows,
-                                          bool& alone) {
-    int first, tiles, end;
+                                          int& tiles, int& last) {
+    int first, end;
     find_expert(tile_off, offsets, N, tile, 1, e, first, tiles, row0, end);
+    last = end - row0 - (tiles - 1) * tile_rows;
     row0 += (tile - first) * tile_rows;
     rows = end - row0 < tile_rows ? end - row0 : tile_rows;
-    alone = tiles == 1;
 }
 
 // Block -> tile mapping.  Blocks are dispatched round-robin over the 8 XCDs (block b runs on
@@ -360,12 +361,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 //
 // Copies: global_load_lds_dwordx4 (no staging registers, no ds_write).  Each copy
 // instruction moves 8 rows x 128 bytes, one whole cache line per row (full lines move more
-// bytes per request than half lines).  With up to three M-tiles per expert the weight copies
-// carry the non-temporal hint: each weight tile is read by the few M-tiles of its expert,
-// close together in time, and streaming it keeps the caches for the token rows and for the
-// other GEMM's operands (measured: down GEMM -8 %, gate/up unchanged); with more M-tiles the
-// tiles are reused enough that the hint costs more than it saves, so the kernel takes it as an
-// argument.  The A half (token rows) and the B half (weight rows) of a k-tile
+// bytes per request than half lines).  While an expert has few M-tiles its weight copies can
+// carry the non-temporal hint: each weight tile is read by one or two tiles, close together in
+// time, and streaming it keeps the caches for the token rows and for the other GEMM's operands
+// (measured with two tiles in step: down GEMM -8 %, gate/up unchanged); with more tiles, or tiles
+// that do not keep step, it costs more than it saves (gemm_dma_body has the rule).
+// The A half (token rows) and the B half (weight rows) of a k-tile
 // are separate 32 KB units of a 5-unit ring; the B half, which usually misses to HBM, is
 // issued two k-tiles ahead of its use and the A half one k-tile ahead.  LDS rows are
 // unpadded (128 B) with their eight 16-byte chunks XOR-swizzled per row so that the 16
@@ -443,8 +444,8 @@ __device__ __forceinline__ void tail_block(const bf16_t* __restrict__ A,
     else tail_task<MODE, 2>(wp, xp, s0, s1, rows, row0, out_ld, out_col, C, lds);
 }
 
-// One 256 x 256 tile.  NTW: the weight copies carry the non-temporal hint (the kernel below picks it
-// by size); ROT: the contraction starts at its k-tile rot (see the pipeline), else at 0.
+// One 256 x 256 tile.  NTW: the weight copies carry the non-temporal hint (the kernel below picks
+// it); ROT: the contraction starts at its k-tile rot (see the pipeline), else at 0.
 template <int MODE, bool NTW, bool ROT>
 __device__ __forceinline__ void gemm_dma_tile(const bf16_t* __restrict__ A,
                                               const int* __restrict__ row_token,
@@ -712,12 +713,12 @@ __device__ __forceinline__ void gemm_dma_tile(const bf16_t* __restrict__ A,
     }
 }
 
-template <int MODE, bool NTW>
+template <int MODE>
 __device__ __forceinline__ void gemm_dma_body(
     const bf16_t* __restrict__ A, const int* __restrict__ row_token,
     const bf16_t* __restrict__ B, const int* __restrict__ offsets,
     const int* __restrict__ tile_off, const int* __restrict__ tail_list, int big_blocks,
-    int N, int d, int m, bf16_t* __restrict__ C, char* sm_bytes) {
+    int N, int d, int m, bf16_t* __restrict__ C, char* sm_bytes, bool nt_weights) {
     constexpr int TM = 256, TN = 256, TK = 64;
     if ((int)blockIdx.x >= big_blocks) {  // the remainder blocks after the tiles
         tail_block<MODE>(A, row_token, B, offsets, tail_list, (int)blockIdx.x - big_blocks, d,
@@ -728,34 +729,53 @@ __device__ __forceinline__ void gemm_dma_body(
     const int nt_count = (MODE == 0) ? m / 128 : (d + TN - 1) / TN;
     int tile, ntile;
     if (!xcd_tile(blockIdx.x, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
-    int e, row0, rows;
-    bool alone;
-    find_tile(tile_off, offsets, N, tile, TM, e, row0, rows, alone);
+    int e, row0, rows, tiles, last;
+    find_tile(tile_off, offsets, N, tile, TM, e, row0, rows, tiles, last);
 
     const int Kd = (MODE == 0) ? d : m;
-    const int rot = alone && (ntile & 1) ? Kd / TK / 2 : 0;  // see the pipeline below
+    const int rot = tiles == 1 && (ntile & 1) ? Kd / TK / 2 : 0;  // see the pipeline below
     // An expert's last tile with at most 128 rows: the smaller tile forms of the mid-sized kernel,
     // as wide as this one's, 3 x (16 + 32) KB of LDS at most (64 rows: per k-tile 40 KB copied and
-    // 64 KB read instead of 64 and 128, and a quarter of the MFMAs).  OLMoE-shaped layer, us:
-    // 2300 tokens 380 -> 360, 8192 tokens top-8 950 -> 907, 16384 tokens 1603 -> 1572; the sizes
-    // without such tiles as before.  Taken in order: all of them after the full tiles would
-    // balance the units better, but reads their experts' weights from HBM again (3000 tokens 391
-    // -> 439, 4096 top-8 496 -> 490).
+    // 64 KB read instead of 64 and 128, and a quarter of the MFMAs).  Taken in order: all of them
+    // after the full tiles would balance the units better, but reads their experts' weights from
+    // HBM again (3000 tokens 391 -> 439, 4096 top-8 496 -> 490).
+    //
+    // The non-temporal hint (where nt_weights allows it) goes to the weights of experts with one
+    // tile, which nobody else reads, and with two tiles of the full form, which walk the weights
+    // in step.  A short tile does not keep step with the full one beside it, and three tiles
+    // drift apart: with the hint the tile that comes first leaves nothing in L2 for the others,
+    // and each of them reads HBM.  OLMoE-shaped layer, us, all tiles of the full form / short
+    // forms, every tile with the hint / this rule: top-8 2048 tokens 310 / 307 / 297, 2300 387 /
+    // 378 / 347, 2816 388 / 381 / 366, 3000 391 / 395 / 388, 4500 577 / 573 / 546, 5000 596 / 606 /
+    // 588, elbow 2300 379 / 359 / 335, 3000 389 / 381 / 367; 8192 top-8 and 16384 tokens, which
+    // have no hint, 939 / 898 and 1605 / 1579.  (Two full tiles without the hint: 3500 tokens
+    // top-8 404 -> 411.)
+    const bool nt = nt_weights && (tiles == 1 || (tiles == 2 && last > 128));
     if (rows <= 128) {
         if (rows <= 64)
             gemm_mid_body<MODE, 64, TN, 1>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
-                                           sm_bytes, NTW);
+                                           sm_bytes, nt);
         else
             gemm_mid_body<MODE, 128, TN, 2>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
-                                            sm_bytes, NTW);
+                                            sm_bytes, nt);
         return;
     }
-    if (rot)  // (a form of its own: the wrap cost the loop 0.5 % at 4096 tokens)
-        gemm_dma_tile<MODE, NTW, true>(A, row_token, B, e, ntile, row0, rows, rot, d, m, C,
-                                       sm_bytes);
-    else
-        gemm_dma_tile<MODE, NTW, false>(A, row_token, B, e, ntile, row0, rows, 0, d, m, C,
-                                        sm_bytes);
+    // (rotation and hint are forms of their own: the wrap cost the loop 0.5 % at 4096 tokens)
+    if (rot) {
+        if (nt)
+            gemm_dma_tile<MODE, true, true>(A, row_token, B, e, ntile, row0, rows, rot, d, m, C,
+                                            sm_bytes);
+        else
+            gemm_dma_tile<MODE, false, true>(A, row_token, B, e, ntile, row0, rows, rot, d, m, C,
+                                             sm_bytes);
+    } else {
+        if (nt)
+            gemm_dma_tile<MODE, true, false>(A, row_token, B, e, ntile, row0, rows, 0, d, m, C,
+                                             sm_bytes);
+        else
+            gemm_dma_tile<MODE, false, false>(A, row_token, B, e, ntile, row0, rows, 0, d, m, C,
+                                              sm_bytes);
+    }
 }
 
 template <int MODE>
@@ -767,12 +787,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // One array: its address is passed to the copy instructions (inline assembly), which tells
     // the compiler that all of it may be written there.
     __shared__ __attribute__((aligned(1024))) char sm_bytes[5 * 256 * 64 * 2];
-    if (nt_weights)  // kernel-uniform
-        gemm_dma_body<MODE, true>(A, row_token, B, offsets, tile_off, tail_list, big_blocks, N,
-                                  d, m, C, sm_bytes);
-    else
-        gemm_dma_body<MODE, false>(A, row_token, B, offsets, tile_off, tail_list, big_blocks, N,
-                                   d, m, C, sm_bytes);
+    gemm_dma_body<MODE>(A, row_token, B, offsets, tile_off, tail_list, big_blocks, N, d, m, C,
+                        sm_bytes, nt_weights);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -807,9 +823,8 @@ __global__ __launch_bounds__(256) void gemm_f32(const float* __restrict__ A,
     int tile, ntile;
     const int block = blockIdx.y * kTileGridRow + blockIdx.x;
     if (!xcd_tile(block, tile_off[N] * nt_count, nt_count, tile, ntile)) return;
-    int e, row0, rows;
-    bool alone;
-    find_tile(tile_off, offsets, N, tile, FBM, e, row0, rows, alone);
+    int e, row0, rows, tiles, last;
+    find_tile(tile_off, offsets, N, tile, FBM, e, row0, rows, tiles, last);
     const int lane = threadIdx.x & 63;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wid >> 1, wn = wid & 1;
