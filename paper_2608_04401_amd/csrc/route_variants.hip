@@ -63,7 +63,9 @@ __device__ __forceinline__ void first_k_experts(const float (&key)[NP], const fl
 // b_(KM - 1 - i) are the KM largest of two descending groups, in a bitonic order that log2(KM)
 // stages of comparators sort.  528 min/max for the 8 largest of 64 and 744 for the 16 largest,
 // where K - k passes over the draws, each a masked minimum with its index, took some 450
-// instructions each (65536 tokens, N = 64, K = 8: angle and tail randomisation 35.7 -> 25.9 us).
+// instructions each (65536 tokens, N = 64, K = 8: angle and tail randomisation 35.7 -> 24.0 us;
+// with K <= 2 a bound of 8 costs more than the pass it replaces: 299776 tokens, N = 32, tail
+// randomisation 17.9 us by passes, 31.8 with KM = 8).
 template <int NP, int KM>
 __device__ __forceinline__ void largest_desc(float (&v)[NP]) {
 #pragma unroll
@@ -90,7 +92,7 @@ __device__ __forceinline__ void largest_desc(float (&v)[NP]) {
 // and theta bits, at two instructions per comparator): for the elbow angle (no selection), and
 // for tail randomisation with K <= kLaneMaxK, whose first k experts are then recovered by the
 // routing kernel's selection rule.
-// KMAX (keys alone): a bound on K, 8 or kLaneMaxK
+// KMAX (keys alone): a bound on K: 2, 4, 8 or kLaneMaxK
 template <int NP, bool FULL, bool PAIRS, int KMAX>
 __global__ __launch_bounds__(256) void route_pair_kernel(
     const float* __restrict__ logits, const float* __restrict__ rand, int64_t T, int N, int K,
@@ -117,10 +119,15 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
     const int64_t t = t0 + (active ? lane : 0);
     const int Nn = FULL ? NP : N;
 
-    // tail randomisation from sorted keys: the lane's draws, loaded before the sort, which they
-    // arrive behind (16-byte loads where every row starts on a 16-byte boundary)
+    // Tail randomisation from sorted keys: the lane's draws (16-byte loads where every row starts
+    // on a 16-byte boundary).  Whole tiles load them where a token of the wave has a tail: a
+    // batch of several waves per SIMD hides the wait, and a wave without a tail reads none.
+    // Otherwise, whose 4-byte loads take longer, they are loaded ahead of the sort, except with
+    // K <= 2, where most waves have no tail (299776 tokens, us, ahead / where needed: N = 32, K = 2
+    // 27.5 / 14.0, K = 8 40.7 / 30.9; N = 24, K = 2 34.6 / 25.4, K = 8 47.8 / 53.7).
+    constexpr bool kEarlyDraws = !FULL && KMAX > 2;
     float draw[NP];
-    if (!PAIRS && rand) {
+    auto load_draws = [&]() {
         const float* const rr = rand + t * N;
         if (FULL && ((uintptr_t)rand % 16) == 0) {
 #pragma unroll
@@ -132,7 +139,8 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
 #pragma unroll
             for (int c = 0; c < NP; ++c) draw[c] = (c < Nn) ? rr[c] : INFINITY;
         }
-    }
+    };
+    if (!PAIRS && kEarlyDraws && rand) load_draws();
 
     // ---- sort (key, id) pairs: rank r holds key[r] and id[r] ----
     float key[NP];
@@ -216,57 +224,64 @@ __global__ __launch_bounds__(256) void route_pair_kernel(
         int cid[KM];
         float ck[KM];
         first_k_experts<NP, KM>(key, okey, row, Nn, k, taken, cid, ck);
-        float dkey[NP], top[NP];  // negated draws (-inf: taken or past N), the KM largest sorted
-#pragma unroll
-        for (int c = 0; c < NP; ++c) {
-            // order_key: a draw of 0 gives +0; the bound keeps an infinite draw above the taken
-            const float q = fmaxf(order_key(-draw[c]), -FLT_MAX);
-            dkey[c] = (c < Nn && !((taken >> c) & 1ull)) ? q : -INFINITY;
-            top[c] = dkey[c];
-        }
-        largest_desc<NP, KM>(top);
         const int n_tail = K - k;  // 0 .. KM - 1
-        uint64_t sel = select_first_k<NP, KM>(
-            top, [&](int c) { return dkey[c]; }, Nn, n_tail > 0 ? n_tail : 1);
-        if (n_tail == 0) sel = 0;
-        int did[KM];
-        float dk[KM];
-        selected_in_id_order<KM>(
-            sel, [&](int c) { return fmaxf(order_key(-rand[t * N + c]), -FLT_MAX); }, Nn, n_tail,
-            did, dk);
-        // the tail in its order: tail[j] for j < n_tail
         int tail[KM];
-        bool distinct = true;
-#pragma unroll
-        for (int j = 0; j + 1 < KM; ++j)
-            if (j + 1 < n_tail && top[j] == top[j + 1]) distinct = false;
-        if (__builtin_expect(__all(distinct), 1)) {
-#pragma unroll
-            for (int j = 0; j < KM; ++j) {
-                tail[j] = did[0];
-#pragma unroll
-                for (int q = 0; q < KM; ++q) tail[j] = (dk[q] == top[j]) ? did[q] : tail[j];
-            }
-        } else {  // by counting (equal draws: lower id, i.e. lower position, first)
-            int rank[KM];
-#pragma unroll
-            for (int q = 0; q < KM; ++q) {
-                rank[q] = q < n_tail ? 0 : KM;
-#pragma unroll
-                for (int o = 0; o < KM; ++o)
-                    if (o != q && o < n_tail && (o < q ? dk[o] >= dk[q] : dk[o] > dk[q]))
-                        ++rank[q];
-            }
-#pragma unroll
-            for (int j = 0; j < KM; ++j) {
-                tail[j] = did[0];
-#pragma unroll
-                for (int q = 0; q < KM; ++q) tail[j] = (rank[q] == j) ? did[q] : tail[j];
-            }
-        }
         float tu[KM];
+        // wave-uniform; tail and tu are read for j < n_tail only.  (With K above 8 and the draws at
+        // hand the test costs more than it saves: N = 60, K = 16 161 / 166 us.)
+        if ((kEarlyDraws && KMAX > 8) || __any(n_tail > 0)) {
+            if (!kEarlyDraws) load_draws();
+            // negated draws (-inf: taken or past N), and the KM largest of them sorted
+            float dkey[NP], top[NP];
 #pragma unroll
-        for (int j = 0; j < KM; ++j) tu[j] = rel_exp(order_key(row[tail[j]]), nl);
+            for (int c = 0; c < NP; ++c) {
+                // order_key: a draw of 0 gives +0; the bound keeps an infinite draw above the
+                // taken
+                const float q = fmaxf(order_key(-draw[c]), -FLT_MAX);
+                dkey[c] = (c < Nn && !((taken >> c) & 1ull)) ? q : -INFINITY;
+                top[c] = dkey[c];
+            }
+            largest_desc<NP, KM>(top);
+            uint64_t sel = select_first_k<NP, KM>(
+                top, [&](int c) { return dkey[c]; }, Nn, n_tail > 0 ? n_tail : 1);
+            if (n_tail == 0) sel = 0;
+            int did[KM];
+            float dk[KM];
+            selected_in_id_order<KM>(
+                sel, [&](int c) { return fmaxf(order_key(-rand[t * N + c]), -FLT_MAX); }, Nn,
+                n_tail, did, dk);
+            // the tail in its order: tail[j] for j < n_tail
+            bool distinct = true;
+#pragma unroll
+            for (int j = 0; j + 1 < KM; ++j)
+                if (j + 1 < n_tail && top[j] == top[j + 1]) distinct = false;
+            if (__builtin_expect(__all(distinct), 1)) {
+#pragma unroll
+                for (int j = 0; j < KM; ++j) {
+                    tail[j] = did[0];
+#pragma unroll
+                    for (int q = 0; q < KM; ++q) tail[j] = (dk[q] == top[j]) ? did[q] : tail[j];
+                }
+            } else {  // by counting (equal draws: lower id, i.e. lower position, first)
+                int rank[KM];
+#pragma unroll
+                for (int q = 0; q < KM; ++q) {
+                    rank[q] = q < n_tail ? 0 : KM;
+#pragma unroll
+                    for (int o = 0; o < KM; ++o)
+                        if (o != q && o < n_tail && (o < q ? dk[o] >= dk[q] : dk[o] > dk[q]))
+                            ++rank[q];
+                }
+#pragma unroll
+                for (int j = 0; j < KM; ++j) {
+                    tail[j] = did[0];
+#pragma unroll
+                    for (int q = 0; q < KM; ++q) tail[j] = (rank[q] == j) ? did[q] : tail[j];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < KM; ++j) tu[j] = rel_exp(order_key(row[tail[j]]), nl);
+        }
         float denom = S;
         if (renorm) {
             float sel_u[KM];
@@ -399,18 +414,16 @@ void launch_pair_np(const float* logits, const float* rand, int64_t T, int N,
     const dim3 grid((unsigned)((waves + 3) / 4));
     // keys only: the elbow angle (no ids), or tail randomisation with K <= kLaneMaxK
     const bool keys_only = !ids || (rand && p.K <= kLaneMaxK);
-    if (!keys_only)
-        ELB_LAUNCH((route_pair_kernel<NP, FULL, true, NP>), grid, dim3(256), 0, s, logits,
-                           rand, T, N, p.K, p.eps, p.mode, p.renormalize, vec4, make_xtable(N),
-                           k, ids, w, e, theta);
-    else if (ids && p.K > 8)
-        ELB_LAUNCH((route_pair_kernel<NP, FULL, false, kLaneMaxK>), grid, dim3(256), 0, s,
-                           logits, rand, T, N, p.K, p.eps, p.mode, p.renormalize, vec4,
-                           make_xtable(N), k, ids, w, e, theta);
-    else
-        ELB_LAUNCH((route_pair_kernel<NP, FULL, false, 8>), grid, dim3(256), 0, s, logits,
-                           rand, T, N, p.K, p.eps, p.mode, p.renormalize, vec4,
-                           make_xtable(N), k, ids, w, e, theta);
+    auto launch = [&](auto kernel) {
+        ELB_LAUNCH(kernel, grid, dim3(256), 0, s, logits, rand, T, N, p.K, p.eps, p.mode,
+                   p.renormalize, vec4, make_xtable(N), k, ids, w, e, theta);
+    };
+    if (!keys_only) launch(route_pair_kernel<NP, FULL, true, NP>);
+    else if (!ids) launch(route_pair_kernel<NP, FULL, false, 8>);  // no K
+    else if (p.K <= 2) launch(route_pair_kernel<NP, FULL, false, 2>);
+    else if (p.K <= 4) launch(route_pair_kernel<NP, FULL, false, 4>);
+    else if (p.K <= 8) launch(route_pair_kernel<NP, FULL, false, 8>);
+    else launch(route_pair_kernel<NP, FULL, false, kLaneMaxK>);
 }
 
 }  // namespace

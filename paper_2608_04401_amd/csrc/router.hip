@@ -429,9 +429,10 @@ __global__ __launch_bounds__(256) void route_split_sum_x16(const float* __restri
 // logits past N are -inf: they sort last, add exact zeros to S and never win the argmin, so
 // every N gives the bits of the one-lane routing.  The MFMA chains, the sum
 // ((P0 + P1) + P2) + P3 and the 16-lane routing (route_token_x16) are those of
-// router_split_bf16 + route_split_sum_x16, so the logits, k, ids and weights are the same bits.  hist (optional): the block's per-expert assignment
-// counts go to histogram b % 4, row b / 4, as route_split_sum_x16 writes them (the grid has
-// four blocks per 64-token group; blocks past the last token write zero counts).
+// router_split_bf16 + route_split_sum_x16, so the logits, k, ids and weights are the same bits.
+// hist (optional): the block's per-expert assignment counts go to histogram b % 4, row b / 4, as
+// route_split_sum_x16 writes them (the grid has four blocks per 64-token group; blocks past the
+// last token write zero counts).
 constexpr int kDmaRing = 4;                // chunks in a wave's ring
 
 // FULL: N == 64 and d % 256 == 0 (no expert past N, no half chunk), without those tests

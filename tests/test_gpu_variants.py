@@ -252,6 +252,25 @@ def test_tail_random_tied_and_neg_inf_logits(N, K):
                     % (N, K, renorm))
 
 
+@pytest.mark.parametrize("N", [8, 21, 32, 64])
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5])
+def test_tail_random_small_caps(N, K):
+    """Caps on both sides of the 2 and 4 largest draws the small networks keep; waves in which
+    no token has a tail, all have one and some do, tied draws and logits among them."""
+    T = 3000
+    lg = synth.planted_logits(T, N, seed=10 * N + K, m_max=min(8, N))
+    lg[:128] = np.arange(N, 0, -1) * 0.01        # a straight curve: one expert or the cap
+    lg[128:256] = 0.0
+    lg[128:256, ::3] = 9.0                       # equal heads: the elbow past the cap
+    lg[256:320, 0] = 30.0                        # one expert
+    lg[1000:1500] = np.round(lg[1000:1500])
+    rand = synth.uniform_draws(T, N, seed=N + K)
+    rand[500:1200] = np.round(rand[500:1200] * 4) / 4
+    for renorm in (False, True):
+        _check_tail(lg.astype(np.float32), rand.astype(np.float32), K, renorm,
+                    "N=%d K=%d renorm=%d" % (N, K, renorm))
+
+
 @pytest.mark.parametrize("T,N,K", [(1, 64, 8), (65, 64, 16), (63, 37, 8), (200, 5, 3), (70, 64, 20)])
 def test_tail_random_draws_end_their_buffer(T, N, K):
     """Logits and draws that end a whole device allocation, with waves of the last block past the
