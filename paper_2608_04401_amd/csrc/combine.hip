@@ -8,7 +8,6 @@
 // time: their rows and weights first, then all eight row loads at once, then the FMAs in rank
 // order, so a block waits for memory once per eight experts instead of twice per expert.
 #include "common.h"
-#include "tilegrid.h"
 
 namespace elb {
 
@@ -57,8 +56,7 @@ __global__ __launch_bounds__(256) void combine_bf16(const bf16_t* __restrict__ Y
                                                     const float* __restrict__ w,
                                                     const bf16_t* residual,
                                                     int64_t T, int d, int K, bf16_t* y) {
-    const int64_t t = (int64_t)blockIdx.y * kTileGridRow + blockIdx.x;
-    if (t >= T) return;  // the last row of a grid of several
+    const int64_t t = blockIdx.x;
     const int kt = k[t] < K ? k[t] : K;  // block-uniform
     for (int c = threadIdx.x * 8; c < d; c += 256 * 8) {
         float acc[8];
@@ -105,8 +103,7 @@ __global__ __launch_bounds__(256) void combine_f32(const float* __restrict__ Y,
                                                    const float* __restrict__ w,
                                                    const float* residual,
                                                    int64_t T, int d, int K, float* y) {
-    const int64_t t = (int64_t)blockIdx.y * kTileGridRow + blockIdx.x;
-    if (t >= T) return;  // the last row of a grid of several
+    const int64_t t = blockIdx.x;
     const int kt = k[t] < K ? k[t] : K;  // block-uniform
     for (int c = threadIdx.x * 4; c < d; c += 256 * 4) {
         float4 acc = residual ? *reinterpret_cast<const float4*>(residual + t * d + c)
@@ -138,27 +135,31 @@ __global__ __launch_bounds__(256) void combine_f32(const float* __restrict__ Y,
 hipError_t launch_combine(const void* Y, const int* k, const int* inv, const float* w,
                           const void* residual, int64_t T, int d, int K, int dtype, void* y,
                           hipStream_t s) {
-    if (T == 0) return hipSuccess;
-    // one block per token; from 2^23 tokens on in rows (whose threads stay below 2^32)
-    const dim3 grid(T < kTileGridRow ? (unsigned)T : (unsigned)kTileGridRow,
-                    (unsigned)((T + kTileGridRow - 1) / kTileGridRow));
-    if (dtype == ELB_BF16) {
-        ProfileScope prof("combine_bf16", s);
-        // Y holds at most T K rows of d bf16 values
-        const bool nt = (double)T * K * d * 2 > (double)kLastLevelCacheBytes;
-        if (nt)
-            ELB_LAUNCH(combine_bf16<true>, grid, dim3(256), 0, s, (const bf16_t*)Y,
-                       k, inv, w, (const bf16_t*)residual, T, d, K, (bf16_t*)y);
-        else
-            ELB_LAUNCH(combine_bf16<false>, grid, dim3(256), 0, s,
-                       (const bf16_t*)Y, k, inv, w, (const bf16_t*)residual, T, d, K,
-                       (bf16_t*)y);
-    } else {
-        ProfileScope prof("combine_f32", s);
-        ELB_LAUNCH(combine_f32, grid, dim3(256), 0, s, (const float*)Y, k,
-                           inv, w, (const float*)residual, T, d, K, (float*)y);
+    ProfileScope prof(dtype == ELB_BF16 ? "combine_bf16" : "combine_f32", s);
+    // Y holds at most T K rows of d bf16 values
+    const bool nt = (double)T * K * d * 2 > (double)kLastLevelCacheBytes;
+    // one block per token, at most 2^23 tokens a launch: the threads of a launch dimension must
+    // stay below 2^32 (above, it silently runs their number modulo 2^32)
+    constexpr int64_t kTokens = (int64_t)1 << 23;
+    for (int64_t t0 = 0; t0 < T; t0 += kTokens) {
+        const dim3 grid((unsigned)(T - t0 < kTokens ? T - t0 : kTokens));
+        const int* const kt = k + t0;
+        const int* const it = inv ? inv + t0 * K : nullptr;
+        const float* const wt = w + t0 * K;
+        const int64_t row = t0 * d, y_row = inv ? 0 : t0 * K * d;
+        if (dtype == ELB_BF16) {
+            const bf16_t* const Yt = (const bf16_t*)Y + y_row;
+            const bf16_t* const rt = residual ? (const bf16_t*)residual + row : nullptr;
+            ELB_LAUNCH((nt ? combine_bf16<true> : combine_bf16<false>), grid, dim3(256), 0, s, Yt,
+                       kt, it, wt, rt, T, d, K, (bf16_t*)y + row);
+        } else {
+            const float* const rt = residual ? (const float*)residual + row : nullptr;
+            ELB_LAUNCH(combine_f32, grid, dim3(256), 0, s, (const float*)Y + y_row, kt, it, wt, rt,
+                       T, d, K, (float*)y + row);
+        }
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace elb

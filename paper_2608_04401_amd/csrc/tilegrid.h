@@ -3,7 +3,6 @@
 // above that silently starts the number modulo 2^32), so the number is cut into rows; x is a
 // multiple of 8 in either case, which keeps block b on XCD b % 8.  May start up to a row of blocks
 // too many: each tests its number against the tile count.
-// The combine numbers its blocks (one per token) in the same rows.
 // Usable from host code without HIP (for tests).
 #pragma once
 
