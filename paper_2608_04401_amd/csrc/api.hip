@@ -287,7 +287,8 @@ int elb_router_route(const void* x, const void* W_router, int64_t T, int32_t d, 
     if (T == 0) return ELB_OK;
     if (!x || !W_router || !k || !ids || !w)
         return fail(ELB_ERR_INVALID_ARG, "NULL tensor pointer");
-    if (router_route_dma_usable(dtype, T, d, N, params->K) && aligned16(x, W_router))
+    if (router_route_dma_usable(dtype, T, d, N, params->K) && aligned16(x, W_router) &&
+        !router_route_small(T, d, N))
         return hip_status(launch_router_route_dma(x, W_router, T, d, N, *params, logits_out, k,
                                                   ids, w, nullptr, 0, (hipStream_t)stream),
                           "router_route");
@@ -488,7 +489,10 @@ static int moe_forward_entry(const void* x, const void* W_router, const void* W_
     // launches, histogram included); the rest, and rows off a 16-byte boundary, the fused
     // one-block kernel, or the router and routing kernels for fp32 and caps above 16.
     const bool aligned = aligned16(x, W_router);
-    if (aligned && router_route_dma_usable(dtype, T, d, N, K)) {
+    // (decode-sized calls have no dispatch that would take the histogram)
+    const bool one_kernel = gemm_use_skinny(dtype, T, K, N, d, m) &&
+                            router_route_small(T, d, N);
+    if (aligned && !one_kernel && router_route_dma_usable(dtype, T, d, N, K)) {
         if (int rc = hip_status(
                 launch_router_route_dma(x, W_router, T, d, N, *params, logits_out, k, ids, w,
                                         (int*)(ws + L.hist), dispatch_hist_ld(T), s),

@@ -124,6 +124,12 @@ constexpr int64_t kRouteDmaMaxT = 4096;
 static_assert(kRouteDmaMaxT <= 64 * kDirectGroups, "the one-launch form writes kHistSubs "
                                                    "histograms");
 bool router_route_dma_usable(int dtype, int64_t T, int d, int N, int K);
+// where the one-kernel router is the faster of the two unless the histogram is wanted: short
+// rows and so few experts that the one-lane sort of them is shorter than the 16-lane sort of 64
+// (us, 16-lane form / one-kernel router: 1 token, d = 256, N = 8 8.7 / 7.4, N = 16 9.3 / 8.7; 4096
+// tokens, d = 64, N = 8 9.1 / 8.5, N = 16 9.7 / 10.1; 2048 tokens, d = 2048, N = 8 11.6 / 13.2; 64
+// tokens, d = 64, N = 24 9.1 / 11.3)
+bool router_route_small(int64_t T, int d, int N);
 hipError_t launch_router_route_dma(const void* x, const void* Wr, int64_t T, int d, int N,
                                    const elb_route_params& p, float* logits, int* k, int* ids,
                                    float* w, int* hist, int64_t hist_ld, hipStream_t s);

@@ -55,9 +55,9 @@ __device__ __forceinline__ float order_key(float f) { return f + 0.0f; }
 // order_key of any bits: a NaN counts as -inf.  No result is promised for a NaN logit, but with
 // every key ordered the k selected experts are k different ones below N, so that a histogram
 // taken from the selection counts what the dispatch finds in ids (a surplus count would leave
-// rows of the expert lists unwritten).  For the kernels that take one, and where pads take part
-// in the sort; a token by 16 lanes has 4 keys a lane, so it costs nothing there.  (An integer
-// test, because one file is built without NaN semantics.)
+// rows of the expert lists unwritten).  For the fused routers' lane kernels, one of which takes a
+// histogram, and where pads take part in the sort of whole (key, id) pairs, whose ids are always
+// different.  (An integer test, because one file is built without NaN semantics.)
 __device__ __forceinline__ float order_key_any(float f) {
     const int i = __float_as_int(f);
     return order_key(__int_as_float((i & 0x7fffffff) > 0x7f800000 ? (int)0xff800000 : i));
@@ -366,18 +366,20 @@ __device__ __forceinline__ void select_emit(const float (&key)[NP], OKey&& okey,
 }
 
 // Token t's routing from row[0..N) (LDS).  FULL: N == NP, so every "position < N" test is
-// static; KMAX: a bound on K (8 or 16).  Writes k[t], ids[t, 0..K), w[t, 0..K).
-template <int NP, bool FULL, int KMAX>
+// static; KMAX: a bound on K (8 or 16); ANY: NaN logits select as order_key_any says.  Writes
+// k[t], ids[t, 0..K), w[t, 0..K).
+template <int NP, bool FULL, int KMAX, bool ANY = false>
 __device__ __forceinline__ void route_token(const float* row, int N, int K, float eps,
                                             int mode, int renorm, const XTable& xt, int64_t t,
                                             int* __restrict__ kout, int* __restrict__ ids,
                                             float* __restrict__ wout) {
     const int Nn = FULL ? NP : N;
+    auto key_of = [&](int c) { return ANY ? order_key_any(row[c]) : order_key(row[c]); };
     // ---- keys of the token's logits (pads are -inf and sort last) ----
     float key[NP], okey[NP];
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
-        okey[c] = (c < Nn) ? order_key(row[c]) : -INFINITY;
+        okey[c] = (c < Nn) ? key_of(c) : -INFINITY;
         key[c] = okey[c];
     }
     sort_desc<NP>(key, std::make_integer_sequence<int, NetHolder<NP>::net.n>{});
@@ -385,8 +387,7 @@ __device__ __forceinline__ void route_token(const float* row, int N, int K, floa
     const int k = sorted_elbow<NP, FULL, KMAX>(key, Nn, K, eps, mode, xt, u, S);
     kout[t] = k;
     select_emit<NP, FULL, KMAX>(
-        key, [&](int c) { return okey[c]; }, [&](int c) { return order_key(row[c]); }, Nn, K,
-        k, u, S, renorm,
+        key, [&](int c) { return okey[c]; }, key_of, Nn, K, k, u, S, renorm,
         [&](int j, int id, float w) {
             ids[t * K + j] = id;
             wout[t * K + j] = w;
@@ -467,7 +468,8 @@ __device__ __forceinline__ void route_token_x16(float* row, int N, int K, float 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int c = 4 * sl + i;
-        v[i] = ((int64_t)ord_flip32(__float_as_int(order_key_any(row[c]))) << 32) |
+        const float f = N == NP ? order_key(row[c]) : order_key_any(row[c]);
+        v[i] = ((int64_t)ord_flip32(__float_as_int(f)) << 32) |
                (uint32_t)(NP - 1 - c);
     }
     // ---- bitonic sort, descending: position p = 4 sl + i ----

@@ -159,8 +159,8 @@ __global__ __launch_bounds__(64 * RW) void router_route_bf16(
                               t0 + tr < T, kout, ids, wout);
     } else {
         if (threadIdx.x < 16 && t0 + threadIdx.x < T)
-            route_token<NP, FULL, KMAX>(&part[0][threadIdx.x][0], N, K, eps, mode, renorm,
-                                        xt, t0 + threadIdx.x, kout, ids, wout);
+            route_token<NP, FULL, KMAX, true>(&part[0][threadIdx.x][0], N, K, eps, mode, renorm,
+                                              xt, t0 + threadIdx.x, kout, ids, wout);
     }
 }
 
@@ -683,6 +683,10 @@ hipError_t launch_router_route(const void* x, const void* Wr, int64_t T, int d, 
     if (p.K <= 8) launch_rr_n<8>(x, Wr, T, d, N, p, logits, k, ids, w, s);
     else launch_rr_n<kLaneMaxK>(x, Wr, T, d, N, p, logits, k, ids, w, s);
     return hipGetLastError();
+}
+
+bool router_route_small(int64_t T, int d, int N) {
+    return d <= 512 && N <= (T <= 64 ? 16 : 8);
 }
 
 bool router_route_dma_usable(int dtype, int64_t T, int d, int N, int K) {

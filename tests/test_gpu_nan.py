@@ -27,12 +27,13 @@ def _in_bounds(k, ids, N, K):
 @pytest.mark.parametrize("T,d,N,K", [(5, 128, 8, 4), (300, 128, 5, 5), (4096, 64, 16, 8),
                                      (333, 128, 60, 16), (1000, 256, 64, 8),
                                      (5000, 256, 64, 8), (9000, 256, 64, 8),
-                                     (9000, 256, 64, 16)])
+                                     (9000, 256, 64, 16), (5000, 128, 60, 8), (8300, 64, 8, 4),
+                                     (4200, 320, 64, 16)])
 @pytest.mark.parametrize("mode", [B.MODE_ELBOW, B.MODE_TOPK])
 def test_layer_with_nan_tokens(T, d, N, K, mode):
-    """One in seven tokens NaN (both signs), in the routers that also write the dispatch
-    histogram: the one-launch form (N < 64 and N = 64) and the split router's two routings
-    (T = 5000 and 9000)."""
+    """One in seven tokens NaN (both signs), in the one-launch router (N < 64 and N = 64), the
+    split router's two routings (T = 5000 and 9000) and the one-kernel router (decode with few
+    experts, and above 4096 tokens)."""
     L = synth.moe_layer(T, d, N, 64, dtype="bf16", seed=T + N)
     x, Wr, Wgu, Wd = (to_gpu(a, BF) for a in (L.x, L.W_router, L.W_gu, L.W_down))
     bad = torch.arange(T, device="cuda") % 7 == 2
