@@ -236,6 +236,11 @@ def elb_elbow_angle(logits: torch.Tensor, eps: float = 1e-8):
     return e, theta
 
 
+@functools.lru_cache(maxsize=256)
+def elb_dispatch_workspace_bytes(T: int, N: int) -> int:
+    return int(lib().elb_dispatch_workspace_bytes(T, N))
+
+
 def elb_dispatch(k: torch.Tensor, ids: torch.Tensor, N: int):
     """-> (counts [N], offsets [N+1], row_token [T*K], inv [T, K]) int32"""
     _dev(k, ids)
@@ -245,9 +250,8 @@ def elb_dispatch(k: torch.Tensor, ids: torch.Tensor, N: int):
     offsets = torch.empty(N + 1, dtype=torch.int32, device=dev)
     row_token = torch.full((T * K,), -1, dtype=torch.int32, device=dev)
     inv = torch.empty((T, K), dtype=torch.int32, device=dev)
-    nb = lib().elb_dispatch_workspace_bytes(T, N)
     stream = _stream()
-    ws = workspace(nb, dev, stream)
+    ws = workspace(elb_dispatch_workspace_bytes(T, N), dev, stream)
     _check("elb_dispatch", lib().elb_dispatch(_ptr(k), _ptr(ids), T, N, K, _ptr(counts),
                                               _ptr(offsets), _ptr(row_token), _ptr(inv),
                                               _ptr(ws), ws.numel(), stream))
