@@ -188,8 +188,9 @@ def test_one_kernel_router_above_4096_tokens(T, d, N, K, mode, eps, renorm):
 @pytest.mark.parametrize("N,K", [(5, 3), (24, 8), (60, 8)])
 def test_one_launch_router_ties(N, K):
     """Equal logits (identical W_r rows in pairs, and a zero token whose logits are all equal):
-    ties go to the lower id and a flat curve to k = 1, as in the one-lane kernels."""
-    T, d = 50, 128
+    ties go to the lower id and a flat curve to k = 1, as in the one-lane kernels.  (d = 544: with
+    at most 512 columns N = 5 takes the one-kernel router.)"""
+    T, d = 50, 544
     L = synth.moe_layer(T, d, N, 64, dtype="bf16", seed=N)
     L.W_router[1::2] = L.W_router[0:N - 1:2][: len(L.W_router[1::2])]
     L.x[7] = 0.0
