@@ -38,7 +38,8 @@
 // 114 / 108, 16 126 / 125; from there on the ranges are faster (20 tokens 128 / 129, 64 133 / 139).
 // Small layers, whose time is not the stream's, lose by it (d = 2048, N = 8, m = 576: 29.8 / 30.5;
 // d = 1024, N = 64, m = 768, 302 MB of weights: 54.2 / 54.7), so it takes twice the last-level
-// cache of weights.
+// cache of weights; and one token's experts are as many different ones, which the ranges deal out
+// as evenly (33.1 / 33.8).
 //
 // Measured (OLMoE-shaped layer, T = 64, gate/up + down): 126 + 54 us with one wave per 64-row
 // task loading operands straight into registers, 79 + 42 us (6.8 and 6.4 TB/s of weights, the
@@ -363,7 +364,7 @@ hipError_t launch_gemm_skinny(const void* x, const void* Wgu, const void* Wd, co
                               void* Y, int* counts, hipStream_t s) {
     const int t = (int)T;
     const int ne = T * K < N ? (int)(T * K) : N;  // see the kernel: tasks by slot or by expert
-    const int spread = T * K <= 2 * N &&
+    const int spread = T > 1 && T * K <= 2 * N &&
                        (double)N * d * m * 6 > 2.0 * (double)kLastLevelCacheBytes;
     {
         ProfileScope prof("gemm_gate_up_skinny", s);
