@@ -713,12 +713,14 @@ __device__ __forceinline__ void gemm_dma_tile(const bf16_t* __restrict__ A,
     }
 }
 
-template <int MODE>
+// NTOK: weight copies may carry the non-temporal hint (a form of its own without: tested in the
+// kernel, the batches that never use it ran 0.3 % slower)
+template <int MODE, bool NTOK>
 __device__ __forceinline__ void gemm_dma_body(
     const bf16_t* __restrict__ A, const int* __restrict__ row_token,
     const bf16_t* __restrict__ B, const int* __restrict__ offsets,
     const int* __restrict__ tile_off, const int* __restrict__ tail_list, int big_blocks,
-    int N, int d, int m, bf16_t* __restrict__ C, char* sm_bytes, bool nt_weights) {
+    int N, int d, int m, bf16_t* __restrict__ C, char* sm_bytes) {
     constexpr int TM = 256, TN = 256, TK = 64;
     if ((int)blockIdx.x >= big_blocks) {  // the remainder blocks after the tiles
         tail_block<MODE>(A, row_token, B, offsets, tail_list, (int)blockIdx.x - big_blocks, d,
@@ -740,7 +742,7 @@ __device__ __forceinline__ void gemm_dma_body(
     // after the full tiles would balance the units better, but reads their experts' weights from
     // HBM again (3000 tokens 391 -> 439, 4096 top-8 496 -> 490).
     //
-    // The non-temporal hint (where nt_weights allows it) goes to the weights of experts with one
+    // The non-temporal hint (where NTOK allows it) goes to the weights of experts with one
     // tile, which nobody else reads, and with two tiles of the full form, which walk the weights
     // in step.  A short tile does not keep step with the full one beside it, and three tiles
     // drift apart: with the hint the tile that comes first leaves nothing in L2 for the others,
@@ -750,7 +752,7 @@ __device__ __forceinline__ void gemm_dma_body(
     // 588, elbow 2300 379 / 359 / 335, 3000 389 / 381 / 367; 8192 top-8 and 16384 tokens, which
     // have no hint, 939 / 898 and 1605 / 1579.  (Two full tiles without the hint: 3500 tokens
     // top-8 404 -> 411.)
-    const bool nt = nt_weights && (tiles == 1 || (tiles == 2 && last > 128));
+    const bool nt = NTOK && (tiles == 1 || (tiles == 2 && last > 128));
     if (rows <= 128) {
         if (rows <= 64)
             gemm_mid_body<MODE, 64, TN, 1>(A, row_token, B, e, row0, rows, ntile, rot, d, m, C,
@@ -787,8 +789,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // One array: its address is passed to the copy instructions (inline assembly), which tells
     // the compiler that all of it may be written there.
     __shared__ __attribute__((aligned(1024))) char sm_bytes[5 * 256 * 64 * 2];
-    gemm_dma_body<MODE>(A, row_token, B, offsets, tile_off, tail_list, big_blocks, N, d, m, C,
-                        sm_bytes, nt_weights);
+    if (nt_weights)  // kernel-uniform
+        gemm_dma_body<MODE, true>(A, row_token, B, offsets, tile_off, tail_list, big_blocks, N,
+                                  d, m, C, sm_bytes);
+    else
+        gemm_dma_body<MODE, false>(A, row_token, B, offsets, tile_off, tail_list, big_blocks, N,
+                                   d, m, C, sm_bytes);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -57,11 +57,8 @@ __device__ __forceinline__ float order_key(float f) { return f + 0.0f; }
 // taken from the selection counts what the dispatch finds in ids (a surplus count would leave
 // rows of the expert lists unwritten).  For the fused routers' lane kernels, one of which takes a
 // histogram, and where pads take part in the sort of whole (key, id) pairs, whose ids are always
-// different.  (An integer test, because one file is built without NaN semantics.)
-__device__ __forceinline__ float order_key_any(float f) {
-    const int i = __float_as_int(f);
-    return order_key(__int_as_float((i & 0x7fffffff) > 0x7f800000 ? (int)0xff800000 : i));
-}
+// different; not for the file that is built without NaN semantics.
+__device__ __forceinline__ float order_key_any(float f) { return fmaxf(order_key(f), -INFINITY); }
 
 // One comparator of the network: larger value to the lower position (v_max_f32/v_min_f32).
 template <int NP, int Q>
