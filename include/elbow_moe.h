@@ -10,7 +10,8 @@
  * MLP.  Fixed top-K routing (the paper's baseline) runs through the same path.
  *
  * Conventions for every entry point:
- *  - All tensor pointers are DEVICE pointers owned by the caller; row-major, densely packed.
+ *  - All tensor pointers are DEVICE pointers owned by the caller; row-major, densely packed,
+ *    starting at any element boundary (x and weights off a 16-byte boundary run slower kernels).
  *    The library never allocates, frees or synchronises device memory; scratch space
  *    comes only from the caller's workspace, which must be 256-byte aligned (as hipMalloc
  *    and torch allocations are).  Nothing is retained between calls.
